@@ -115,8 +115,10 @@ typedef struct lbm_params {
 /* Byte sizes of the caller-allocated device buffers. */
 typedef struct lbm_sizes {
     uint64_t n_nodes;
-    uint64_t pop_bytes;     /* each of the two population buffers (A and B): 54 planes of
-                               (nx+2)(ny+2)(nz+2) padded nodes in the storage format
+    uint64_t pop_bytes;     /* each of the two population buffers (A and B): 54 values per
+                               node of the (nx+2)(ny+2)(nz+2) padded lattice in the storage
+                               format (the planes that init and set_state write; a step
+                               writes rows that hold the 27 values of their nodes)
                                (D3Q19: the larger of 39 planes of N floats, the form
                                init and set_state write, and the 19 planes plus a 16-byte
                                record per node that a step writes) */
@@ -130,10 +132,11 @@ typedef struct lbm_sizes {
     uint64_t adjoint_bytes; /* adjoint work buffer (see lbm_adjoint_step) */
     uint64_t state_bytes;   /* a full FP32 state: 2Q floats per node (fr[Q], fb[Q]) */
     uint64_t snap_bytes;    /* one state snapshot in the library's own layout (see lbm_step_into):
-                               27 population planes of (nx+2)(ny+2)(nz+2) padded nodes in the
-                               storage format (28 for BF16_EQ / FP16_EQ), a 16-byte record per
-                               padded node (two for BF16_EQ / FP16_EQ), and for the jet one
-                               outlet plane of 54 floats per (x, y): about 124 B per node in FP32 */
+                               space for 27 populations per node of the (nx+2)(ny+2)(nz+2)
+                               padded lattice in the storage format (28 for BF16_EQ /
+                               FP16_EQ), a 16-byte record per padded node (two for BF16_EQ /
+                               FP16_EQ), and for the jet one outlet plane of 54 floats per
+                               (x, y): about 124 B per node in FP32 */
 } lbm_sizes;
 
 /* Device buffers owned by the caller; must stay valid until lbm_destroy(). */
@@ -254,7 +257,7 @@ int lbm_adjoint_step_snapshot(lbm_handle* h, const void* snap_t, int64_t t, cons
 
 /* Instrumentation: with enable != 0, lbm_step records HIP events on its
  * stream around its kernel groups (density pass; fused collide-recolour-
- * stream kernel; boundary kernels: ghost-shell fills);
+ * stream kernel; boundary kernel: the jet's outlet plane and inlet cells);
  * enable == 0 stops recording. */
 int lbm_profile(lbm_handle* h, int enable);
 

@@ -25,8 +25,8 @@ constexpr uint64_t kStaticDiagNodes = 1ull << 22;
 constexpr uint64_t kStaticDiagBytes = diag_bytes(kStaticDiagNodes);
 static __device__ __align__(256) unsigned char scratch[kStaticDiagBytes];
 
-// One complete state: population planes (shifted form, or the general form
-// of 54 planes), the recolouring records R, the reference records of the
+// One complete state: population rows (shifted form) or the 54 padded planes of
+// the general form, the recolouring records R, the reference records of the
 // referenced 16-bit forms, and (jet) the outlet plane the next step's
 // convective condition starts from.
 struct StateSet {
@@ -43,8 +43,8 @@ struct lbm_handle {
     StateSet own[2];    // the handle's A and B sets (caller buffers given to lbm_init)
     StateSet ext;       // a caller snapshot that lbm_step_into made current
     int cs;             // current set: 0 or 1 (own), 2 (ext)
-    float2* PD;         // (phi, rho - rho_b0) per padded node
-    float* XR;          // tagged minority-colour fraction per padded node
+    float2* PD;         // (phi, rho - rho_b0) per node
+    float* XR;          // tagged minority-colour fraction per node
     float2* F2;         // D3Q19: (phi, rho - rho_b0) per node, then (rho_r, rho_b) per node
     double* audit;
     void* adjoint;
@@ -53,19 +53,34 @@ struct lbm_handle {
     long long t;        // time level of the current state
     int unshifted;      // current buffer holds a general state at the node itself
     dim3 grid_all;      // every interior plane
-    dim3 grid_tiles;    // stencil tiles of the fused collision
+    dim3 grid_tiles;    // stencil tiles
+    dim3 grid_ctiles;   // stencil tiles of the fused collision
     dim3 grid_dtiles;   // stencil tiles of the density pass
+    dim3 grid_rows;     // one plane by row segments (outlet)
     dim3 grid_plane;    // one plane
-    dim3 grid_shell;    // ghost shell cells
+    dim3 grid_shell;    // ghost shell cells (adjoint)
     uint32_t ncells;    // ghost shell cell count
-    int nblk;           // blocks of grid_all (audit partial slots)
+    int nblk;           // blocks of grid_all (adjoint partial slots)
+    int tiles;          // tiles of the step kernels (step_tiles)
+    int nt;             // the state is larger than the memory-side cache
+    int naud;           // blocks of the macroscopic kernel (audit partial slots)
     // instrumentation: events around the kernel groups of each step
     int profiling;
-    std::vector<hipEvent_t> ev;  // pool, 5 per recorded step
+    std::vector<hipEvent_t> ev;  // pool, 4 per recorded step
     size_t ev_used;
 };
 
 namespace {
+
+uint64_t blocks_of(dim3 g) { return (uint64_t)g.x * g.y; }
+
+// partial sums of the FP64 audit: one slot per block of the macroscopic kernel
+// (stencil tiles; D3Q19: a flat grid)
+uint64_t audit_blocks(const lbm_params* p)
+{
+    const uint64_t plane = (uint64_t)p->nx * p->ny, flat = (plane + BLOCK - 1) / BLOCK;
+    return p->lattice == 19 ? flat * (uint64_t)p->nz : blocks_of(tile_grid<STX, STY>(p->nx, p->ny, p->nz));
+}
 
 thread_local char g_err[512] = "";
 
@@ -108,6 +123,24 @@ uint64_t padded_nodes(const lbm_params* p)
 }
 
 bool is_q19(const lbm_params* p) { return p->lattice == 19; }
+
+// Stride of a row of nx nodes: nx rounded up to the widest power of two of
+// elements, at most a 128-byte cache line, with which the rows fit the space of
+// the padded lattice that the buffer sizes state (a row of 27 slots per 27 padded
+// nodes, one record per padded node).  Multiples of a line give every row whole
+// lines; where nothing wider fits the stride is nx itself.
+int row_stride(const lbm_params* p)
+{
+    const uint64_t NP = padded_nodes(p), rows = (uint64_t)p->ny * (p->nz + (p->bc == LBM_BC_JET ? 1 : 0));
+    for (int a = (int)(128 / elem_bytes(p->storage)); a > 1; a >>= 1) {
+        const int rs = (p->nx + a - 1) / a * a;
+        if ((uint64_t)rs * rows <= NP) return rs;
+    }
+    return p->nx;
+}
+
+// rows of one set of populations and of every per-node array
+uint64_t row_count(const lbm_params* p) { return (uint64_t)p->ny * (p->nz + (p->bc == LBM_BC_JET ? 1 : 0)); }
 
 int validate(const lbm_params* p)
 {
@@ -170,6 +203,8 @@ void fill_kp(const lbm_params* p, const float* inlet, KP* k)
     k->nz = p->nz;
     k->px = p->nx + 2;
     k->py = p->ny + 2;
+    k->rs = row_stride(p);
+    k->zg = p->bc == LBM_BC_JET ? 1 : 0;
     k->NP = (uint32_t)padded_nodes(p);
     k->plane = (uint32_t)p->nx * (uint32_t)p->ny;
     k->N = k->plane * (uint32_t)p->nz;
@@ -181,7 +216,7 @@ void fill_kp(const lbm_params* p, const float* inlet, KP* k)
     k->nx_mul = (uint32_t)((two + (unsigned long long)p->nx - 1) / (unsigned long long)p->nx);
     k->nx_sh = 31 + L;
     k->z0 = 0;
-    k->ntx = (p->nx + STX - 1) / STX;
+    k->planes = p->nz;
     const double ar = 1.0 - (1.0 - p->alpha_b) * p->rho_b0 / p->rho_r0;
     k->rho_r0 = (float)p->rho_r0;
     k->rho_b0 = (float)p->rho_b0;
@@ -254,6 +289,31 @@ int dispatch(int bc, int storage, F&& f)
     return f(IntC<LBM_BC_JET>{}, StF16Eq{});
 }
 
+// Which tiles the step kernels take: rows of 128 nodes, or rows of 64 where the
+// wavefronts of a row then have a fifth fewer lanes (nx of 1..64 and 129..192).
+// Measured, narrow against wide, FP32: 154x120x422 674 against 713 us, 48x50x190
+// 44 against 52 us; 309x222x205 (a sixth fewer lanes) 1193 against 1170 us,
+// 100x100x100 (none fewer) 71 against 68 us.  The referenced 16-bit forms have
+// tiles of their own (see RefWin).
+enum { TILES_WIDE, TILES_NARROW };
+int step_tiles(const lbm_params* p)
+{
+    const int wide = (p->nx + 127) / 128 * 128, narrow = (p->nx + 63) / 64 * 64;
+    return 4 * wide > 5 * narrow ? TILES_NARROW : TILES_WIDE;
+}
+
+// call f(tiles)
+template <class S, class F>
+int with_tiles(int tiles, F&& f)
+{
+    if constexpr (S::kEqRef) {
+        return f(RefTiles{});
+    } else {
+        if (tiles == TILES_WIDE) return f(WideTiles{});
+        return f(NarrowTiles{});
+    }
+}
+
 bool aligned(const void* ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
 // parameters for reading the current state
@@ -276,9 +336,8 @@ KP read_kp(const lbm_handle* h)
 }
 
 // Layout of a state snapshot (a shifted state, as a step leaves it): the
-// population planes 0..26 (0..27 in the referenced 16-bit forms, whose rest
-// population also uses plane 27) with the plane stride of the population
-// buffers, the recolouring records R, the reference records (referenced
+// population rows (27 slots each, 28 in the referenced 16-bit forms), the
+// recolouring records R, the reference records (referenced
 // forms), and the jet's outlet plane (54 floats per (x, y)); each part
 // 256-byte aligned.  Returns the byte count; with base != NULL fills *s.
 uint64_t snap_layout(const lbm_params* p, char* base, StateSet* s)
@@ -310,10 +369,10 @@ struct SnapBytes {
 };
 SnapBytes snap_bytes_of(const lbm_params* p)
 {
-    const uint64_t NP = padded_nodes(p), plane = (uint64_t)p->nx * p->ny;
+    const uint64_t n = row_count(p) * (uint64_t)row_stride(p), plane = (uint64_t)p->nx * p->ny;
     SnapBytes b;
-    b.pop = (size_t)((eq_ref(p->storage) ? Q + 1 : Q) * NP * elem_bytes(p->storage));
-    b.rec = (size_t)(NP * 16);
+    b.pop = (size_t)((eq_ref(p->storage) ? Q + 1 : Q) * n * elem_bytes(p->storage));
+    b.rec = (size_t)(n * 16);
     b.hist = p->bc == LBM_BC_JET ? (size_t)(2ull * Q * plane * sizeof(float)) : 0;
     return b;
 }
@@ -336,7 +395,7 @@ int lbm_query_sizes(const lbm_params* p, lbm_sizes* out)
         out->pop_bytes = q19::pop_bytes(N);
         out->field_bytes = 16ull * N;
         out->hist_bytes = p->bc == LBM_BC_JET ? 2ull * 2ull * q19::Q19 * plane * sizeof(float) : 0;
-        out->audit_bytes = (nblk + 1) * 5 * sizeof(double);
+        out->audit_bytes = (audit_blocks(p) + 1) * 5 * sizeof(double);
         out->inlet_bytes = plane * sizeof(float);
         out->adjoint_bytes = 0;
         out->state_bytes = 2ull * q19::Q19 * N * sizeof(float);
@@ -346,7 +405,7 @@ int lbm_query_sizes(const lbm_params* p, lbm_sizes* out)
     out->pop_bytes = 2ull * Q * NP * elem_bytes(p->storage);
     out->field_bytes = field_floats(p->storage) * NP * sizeof(float);
     out->hist_bytes = p->bc == LBM_BC_JET ? 2ull * 2ull * Q * plane * sizeof(float) : 0;
-    out->audit_bytes = (nblk + 1) * 5 * sizeof(double);
+    out->audit_bytes = (audit_blocks(p) + 1) * 5 * sizeof(double);
     out->inlet_bytes = plane * sizeof(float);
     out->adjoint_bytes = adjoint_layout(NP, N, plane, nblk, nullptr, nullptr);
     out->state_bytes = 2ull * Q * N * sizeof(float);
@@ -404,12 +463,25 @@ int lbm_init(lbm_handle** h, const lbm_params* p, const lbm_buffers* buf, const 
     const unsigned bx = (H->k.plane + BLOCK - 1) / BLOCK;
     H->grid_all = dim3(bx, p->nz);
     H->grid_plane = dim3(bx, 1);
-    H->grid_tiles = dim3((unsigned)(H->k.ntx * ((p->ny + STY - 1) / STY)), p->nz);
-    H->grid_dtiles = dim3((unsigned)(H->k.ntx * ((p->ny + DTY - 1) / DTY)), p->nz);
+    H->grid_tiles = tile_grid<STX, STY>(p->nx, p->ny, p->nz);
+    H->tiles = step_tiles(p);
+    dispatch(p->bc, p->storage, [&](auto, auto st) -> int {
+        return with_tiles<decltype(st)>(H->tiles, [&](auto tl) -> int {
+            using T = decltype(tl);
+            const int below = p->bc == LBM_BC_JET ? p->nz - 1 : p->nz;  // the outlet plane has its own kernel
+            H->grid_ctiles = tile_grid<T::CX, T::CY>(p->nx, p->ny, p->nz);
+            H->grid_dtiles = tile_grid<T::DX, T::DY>(p->nx, p->ny, below);
+            return LBM_OK;
+        });
+    });
+    H->grid_rows = dim3((unsigned)((p->nx + OBLOCK - 1) / OBLOCK), p->ny);
     const uint64_t cells = 2ull * H->k.px * H->k.py + 2ull * H->k.px * p->nz + 2ull * p->ny * p->nz;
     H->ncells = (uint32_t)cells;
     H->grid_shell = dim3((unsigned)((cells + BLOCK - 1) / BLOCK));
     H->nblk = (int)(H->grid_all.x * H->grid_all.y);
+    H->naud = (int)audit_blocks(p);
+    const SnapBytes sb = snap_bytes_of(p);
+    H->nt = (uint64_t)sb.pop + sb.rec > kCacheBytes;
     if (H->q19) {
         H->F2 = (float2*)buf->fields;
         H->PD = nullptr;
@@ -462,13 +534,8 @@ int q19_launch(lbm_handle* h, const StateSet& dst_set, hipEvent_t* e)
     float* dst = (float*)dst_set.pop;
     const float* hprev = cur_set(h).hist;
     float* hcur = dst_set.hist;
-    // jet: the planes below the outlet, then the outlet plane by its own kernel
+    // jet: the outlet plane by its own kernel, then the planes below it
     const dim3 gd = BC == LBM_BC_JET ? dim3(h->grid_all.x, (unsigned)(h->p.nz - 1)) : h->grid_all;
-    if (h->unshifted)
-        hipLaunchKernelGGL((q19::k19_density<true, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
-    else
-        hipLaunchKernelGGL((q19::k19_density<false, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
-    LAUNCH_CHECK();
     if (BC == LBM_BC_JET) {
         if (h->unshifted)
             hipLaunchKernelGGL(q19::k19_outlet<true>, h->grid_plane, dim3(BLOCK), 0, h->stream, src, h->F2, hprev,
@@ -478,10 +545,13 @@ int q19_launch(lbm_handle* h, const StateSet& dst_set, hipEvent_t* e)
                                hcur, k);
         LAUNCH_CHECK();
     }
-    if (e) {
-        HIP_CHECK(hipEventRecord(e[1], h->stream));
-        HIP_CHECK(hipEventRecord(e[2], h->stream));
-    }
+    if (e) HIP_CHECK(hipEventRecord(e[1], h->stream));
+    if (h->unshifted)
+        hipLaunchKernelGGL((q19::k19_density<true, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
+    else
+        hipLaunchKernelGGL((q19::k19_density<false, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
+    LAUNCH_CHECK();
+    if (e) HIP_CHECK(hipEventRecord(e[2], h->stream));
     if (h->unshifted)
         hipLaunchKernelGGL((q19::k19_collide<true, BC>), h->grid_all, dim3(BLOCK), 0, h->stream, src, dst, h->F2,
                            hcur, k);
@@ -496,22 +566,19 @@ int q19_step(lbm_handle* h, const StateSet& dst_set, int dst_cs)
 {
     hipEvent_t* e = nullptr;
     if (h->profiling) {
-        while (h->ev.size() < h->ev_used + 5) {
+        while (h->ev.size() < h->ev_used + 4) {
             hipEvent_t x;
             HIP_CHECK(hipEventCreate(&x));
             h->ev.push_back(x);
         }
         e = &h->ev[h->ev_used];
-        h->ev_used += 5;
+        h->ev_used += 4;
         HIP_CHECK(hipEventRecord(e[0], h->stream));
     }
     const int rc = h->p.bc == LBM_BC_JET ? q19_launch<LBM_BC_JET>(h, dst_set, e)
                                          : q19_launch<LBM_BC_PERIODIC>(h, dst_set, e);
     if (rc != LBM_OK) return rc;
-    if (e) {
-        HIP_CHECK(hipEventRecord(e[3], h->stream));
-        HIP_CHECK(hipEventRecord(e[4], h->stream));
-    }
+    if (e) HIP_CHECK(hipEventRecord(e[3], h->stream));
     h->cs = dst_cs;
     h->t += 1;
     h->unshifted = 0;
@@ -536,44 +603,43 @@ int step_once(lbm_handle* h, const StateSet& dst_set, int dst_cs)
         float* hcur = dst_set.hist;
         hipEvent_t* e = nullptr;
         if (h->profiling) {
-            while (h->ev.size() < h->ev_used + 5) {
+            while (h->ev.size() < h->ev_used + 4) {
                 hipEvent_t x;
                 HIP_CHECK(hipEventCreate(&x));
                 h->ev.push_back(x);
             }
             e = &h->ev[h->ev_used];
-            h->ev_used += 5;
+            h->ev_used += 4;
             HIP_CHECK(hipEventRecord(e[0], h->stream));
         }
-        // density pass (jet: the outlet plane by the convective condition)
+        // density pass (jet: the outlet plane by the convective condition, and
+        // the inlet cells of the state being written)
+        KP kd = k;
         if (jet) {
-            const dim3 gi(h->grid_dtiles.x, (unsigned)(h->p.nz - 1));
-            const dim3 go((unsigned)((h->k.plane + OBLOCK - 1) / OBLOCK));
-            hipLaunchKernelGGL((k_density<BC, S>), gi, dim3(DBLOCK), 0, h->stream, src, h->PD, h->XR, k,
-                               (float*)nullptr);
+            kd.planes -= 1;
+            hipLaunchKernelGGL((k_outlet<S>), h->grid_rows, dim3(OBLOCK), 0, h->stream, src, h->PD, h->XR, hprev,
+                               hcur, k, (float*)nullptr, dst, Rout, Qout);
             LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_outlet_density<S>), go, dim3(OBLOCK), 0, h->stream, src, h->PD, h->XR, hprev,
-                               hcur, k, (float*)nullptr);
-        } else {
-            hipLaunchKernelGGL((k_density<BC, S>), h->grid_dtiles, dim3(DBLOCK), 0, h->stream, src, h->PD, h->XR,
-                               k, (float*)nullptr);
         }
-        LAUNCH_CHECK();
         if (e) HIP_CHECK(hipEventRecord(e[1], h->stream));
-        if (!kDensityGhosts<S>) {  // FP32: the density kernels fill the field ghost shell
-            hipLaunchKernelGGL(k_field_ghosts<BC>, h->grid_shell, dim3(BLOCK), 0, h->stream, h->PD, k, h->ncells);
+        const int rc = with_tiles<S>(h->tiles, [&](auto tl) -> int {
+            using TL = decltype(tl);
+            hipLaunchKernelGGL((k_density<BC, S, TL>), h->grid_dtiles, dim3(TL::DX * TL::DY), 0, h->stream, src, h->PD,
+                               h->XR, kd, (float*)nullptr);
             LAUNCH_CHECK();
-        }
-        if (e) HIP_CHECK(hipEventRecord(e[2], h->stream));
-        // fused collide-perturb-recolour-stream
-        hipLaunchKernelGGL((k_collide<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream, src, dst, h->PD, h->XR,
-                           hcur, Rout, Qout, k);
-        LAUNCH_CHECK();
+            if (e) HIP_CHECK(hipEventRecord(e[2], h->stream));
+            // fused collide-perturb-recolour-stream
+            if (h->nt)
+                hipLaunchKernelGGL((k_collide<BC, S, TL, true>), h->grid_ctiles, dim3(BLOCK), 0, h->stream, src, dst,
+                                   h->PD, h->XR, hcur, Rout, Qout, k);
+            else
+                hipLaunchKernelGGL((k_collide<BC, S, TL, false>), h->grid_ctiles, dim3(BLOCK), 0, h->stream, src, dst,
+                                   h->PD, h->XR, hcur, Rout, Qout, k);
+            LAUNCH_CHECK();
+            return LBM_OK;
+        });
+        if (rc != LBM_OK) return rc;
         if (e) HIP_CHECK(hipEventRecord(e[3], h->stream));
-        hipLaunchKernelGGL((k_pop_ghosts<BC, S>), dim3((h->ncells + GBLOCK - 1) / GBLOCK), dim3(GBLOCK), 0,
-                           h->stream, dst, Rout, Qout, k, h->ncells);
-        LAUNCH_CHECK();
-        if (e) HIP_CHECK(hipEventRecord(e[4], h->stream));
         if (dst_cs == 2) h->ext = dst_set;
         h->cs = dst_cs;
         h->t += 1;
@@ -683,15 +749,15 @@ int lbm_macroscopic(lbm_handle* h, float* rho_r, float* rho_b, float* u, float* 
     }() : dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
         using S = decltype(st);
         constexpr int BC = decltype(bc)::value;
-        hipLaunchKernelGGL((k_macro<BC, S>), h->grid_all, dim3(BLOCK), 0, h->stream,
+        hipLaunchKernelGGL((k_macro<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                            (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, rho_r, rho_b, u, phi,
                            audit ? h->audit : nullptr);
         LAUNCH_CHECK();
         return LBM_OK;
     });
     if (rc != LBM_OK || !audit) return rc;
-    double* tot = h->audit + (size_t)h->nblk * 5;
-    hipLaunchKernelGGL(k_audit_final, dim3(1), dim3(BLOCK), 0, h->stream, h->audit, h->nblk, tot);
+    double* tot = h->audit + (size_t)h->naud * 5;
+    hipLaunchKernelGGL(k_audit_final, dim3(1), dim3(BLOCK), 0, h->stream, h->audit, h->naud, tot);
     LAUNCH_CHECK();
     HIP_CHECK(hipMemcpyAsync(audit, tot, 5 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIP_CHECK(hipStreamSynchronize(h->stream));
@@ -723,7 +789,7 @@ int lbm_get_state(lbm_handle* h, float* state)
     return dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
         using S = decltype(st);
         constexpr int BC = decltype(bc)::value;
-        hipLaunchKernelGGL((k_get_state<BC, S>), h->grid_all, dim3(BLOCK), 0, h->stream,
+        hipLaunchKernelGGL((k_get_state<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                            (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, state, (double)h->k.rho_b0);
         LAUNCH_CHECK();
         return LBM_OK;
@@ -774,8 +840,6 @@ template <int BC>
 int adjoint_rest(lbm_handle* h, const KP& k, const AdjWork& w, const float* htop, size_t hs, int dfr,
                  const float* lambda_in, float* lambda_out, double* dJ_dA, float* dJ_du_in)
 {
-    hipLaunchKernelGGL(k_field_ghosts<BC>, h->grid_shell, dim3(BLOCK), 0, h->stream, h->PD, k, h->ncells);
-    LAUNCH_CHECK();
     if (BC == LBM_BC_JET) {
         KP kt = k;
         kt.z0 = h->p.nz - 3;
@@ -864,19 +928,20 @@ int lbm_adjoint_step_snapshot(lbm_handle* h, const void* snap_t, int64_t t, cons
         using S = decltype(st);
         constexpr int BC = decltype(bc)::value;
         const typename S::T* src = (const typename S::T*)s.pop;
+        KP kd = k;
         if (BC == LBM_BC_JET) {
-            const dim3 gi(h->grid_dtiles.x, (unsigned)(h->p.nz - 1));
-            const dim3 go((unsigned)((h->k.plane + OBLOCK - 1) / OBLOCK));
-            hipLaunchKernelGGL((k_density<BC, S, true>), gi, dim3(DBLOCK), 0, h->stream, src, h->PD, h->XR, k, w.MOM);
+            kd.planes -= 1;
+            hipLaunchKernelGGL((k_outlet<S>), h->grid_rows, dim3(OBLOCK), 0, h->stream, src, h->PD, h->XR, s.hist,
+                               w.ST, k, w.MOM, (typename S::T*)nullptr, (float4*)nullptr, (uint4*)nullptr);
             LAUNCH_CHECK();
-            hipLaunchKernelGGL((k_outlet_density<S>), go, dim3(OBLOCK), 0, h->stream, src, h->PD, h->XR, s.hist,
-                               w.ST, k, w.MOM);
-        } else {
-            hipLaunchKernelGGL((k_density<BC, S, true>), h->grid_dtiles, dim3(DBLOCK), 0, h->stream, src, h->PD,
-                               h->XR, k, w.MOM);
         }
-        LAUNCH_CHECK();
-        return LBM_OK;
+        return with_tiles<S>(h->tiles, [&](auto tl) -> int {
+            using TL = decltype(tl);
+            hipLaunchKernelGGL((k_density<BC, S, TL, true>), h->grid_dtiles, dim3(TL::DX * TL::DY), 0, h->stream, src,
+                               h->PD, h->XR, kd, w.MOM);
+            LAUNCH_CHECK();
+            return LBM_OK;
+        });
     });
     if (rc != LBM_OK) return rc;
     if (h->p.bc == LBM_BC_PERIODIC)
@@ -898,15 +963,14 @@ int lbm_profile_read(lbm_handle* h, double* ms, int64_t* launches)
     ms[0] = ms[1] = ms[2] = 0.0;
     launches[0] = launches[1] = launches[2] = 0;
     if (h->ev_used) HIP_CHECK(hipEventSynchronize(h->ev[h->ev_used - 1]));
-    for (size_t i = 0; i + 5 <= h->ev_used; i += 5) {
-        float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
-        HIP_CHECK(hipEventElapsedTime(&a, h->ev[i], h->ev[i + 1]));
-        HIP_CHECK(hipEventElapsedTime(&b, h->ev[i + 1], h->ev[i + 2]));
+    for (size_t i = 0; i + 4 <= h->ev_used; i += 4) {
+        float b = 0.f, d = 0.f, c = 0.f;  // boundary, density, fused
+        HIP_CHECK(hipEventElapsedTime(&b, h->ev[i], h->ev[i + 1]));
+        HIP_CHECK(hipEventElapsedTime(&d, h->ev[i + 1], h->ev[i + 2]));
         HIP_CHECK(hipEventElapsedTime(&c, h->ev[i + 2], h->ev[i + 3]));
-        HIP_CHECK(hipEventElapsedTime(&d, h->ev[i + 3], h->ev[i + 4]));
-        ms[0] += a;
+        ms[0] += d;
         ms[1] += c;
-        ms[2] += b + d;
+        ms[2] += b;
         launches[0] += 1;
         launches[1] += 1;
         launches[2] += 1;
@@ -949,7 +1013,7 @@ int diag_run(lbm_handle* h, void* work, lbm_jet_stats* stats, int64_t* volumes, 
         LAUNCH_CHECK();
         const float* hist = cur_set(h).hist;
         if (!h->q19)
-            hipLaunchKernelGGL((k_diag_init<BC, S>), h->grid_all, dim3(BLOCK), 0, h->stream,
+            hipLaunchKernelGGL((k_diag_init<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                (const typename S::T*)cur_set(h).pop, hist, k, w);
         else if (h->unshifted)
             hipLaunchKernelGGL((q19::k19_diag_init<true, BC>), h->grid_all, dim3(BLOCK), 0, h->stream,

@@ -6,8 +6,8 @@
 // and lambda_{t+1} . d x_{t+1}/d u_in (the inlet axial-velocity profile) to the
 // caller's gradient accumulators.  The forward quantities of step t are
 // recomputed from x_t (no tape).  Passes:
-//   1. densities of x_t -> (phi, rho - rho_b0), rho_r/rho per padded node, and the
-//      raw moments of the colour-blind deviations up to second order; ghost shell
+//   1. densities of x_t -> (phi, rho - rho_b0), rho_r/rho per node, and the
+//      raw moments of the colour-blind deviations up to second order
 //   2. (jet) outlet: the convective condition of the outlet plane depends on the
 //      streamed populations of the plane below; its adjoint is formed first
 //      from a forward recomputation of the three top planes
@@ -109,6 +109,7 @@ __global__ __launch_bounds__(BLOCK) void k_adj_density(const float* __restrict__
 }
 
 // forward node quantities of node nd from its moments and the field stencil
+template <int BC>
 __device__ __forceinline__ void adj_node_fwd(const KP& k, const float* __restrict__ MOM,
                                              const float2* __restrict__ PD, const float* __restrict__ XR,
                                              const Node& nd, NodeFwdT<float>& f, float& xr)
@@ -123,7 +124,7 @@ __device__ __forceinline__ void adj_node_fwd(const KP& k, const float* __restric
     xr = ldp(XR, nd.n);
     if (k.xr_tagged) xr = frac_of(xr, 0u);
     double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    gradients(PD, k, nd.n, g);
+    gradients<BC>(PD, k, nd, g);
     node_fwd<float>(k, M, phic, g, f);
 }
 
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(BLOCK) void k_adj_top_post(const float* __restrict_
     if (!nd.valid) return;
     NodeFwdT<float> f;
     float xr;
-    adj_node_fwd(k, MOM, PD, XR, nd, f, xr);
+    adj_node_fwd<LBM_BC_JET>(k, MOM, PD, XR, nd, f, xr);
     float fp[Q], V[3];
     node_post<float>(k, f, xr, fp, V);
     const int zz = nd.z - k.z0;
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     if (nd.valid) {
         NodeFwdT<float> f;
         float xr;
-        adj_node_fwd(k, MOM, PD, XR, nd, f, xr);
+        adj_node_fwd<BC>(k, MOM, PD, XR, nd, f, xr);
         float Lr[Q], Lb[Q];
         adj_gather<BC>(k, lam_in, ML, nd, Lr, Lb);
         NodeAdjT<float> o;
@@ -296,8 +297,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2, 2))) v
         const float lc[10] = {o.Lm0, o.Lj[0], o.Lj[1], o.Lj[2], o.Lq[0], o.Lq[1], o.Lq[2], o.Lq[3], o.Lq[4], o.Lq[5]};
 #pragma unroll
         for (int a = 0; a < 10; ++a) LC[(size_t)a * N + n] = lc[a];
-        stp(AG0, nd.n, make_float4(o.Lgp[0], o.Lgp[1], o.Lgp[2], o.Lphic));
-        stp(AG1, nd.n, make_float4(o.Lgr[0], o.Lgr[1], o.Lgr[2], o.Lxr));
+        const uint32_t pn = pidx(k, nd.x, nd.y, nd.z);
+        stp(AG0, pn, make_float4(o.Lgp[0], o.Lgp[1], o.Lgp[2], o.Lphic));
+        stp(AG1, pn, make_float4(o.Lgr[0], o.Lgr[1], o.Lgr[2], o.Lxr));
         acc[0] = (double)o.LA;
     }
     block_partials<1>(acc, AP, blockIdx.y * gridDim.x + blockIdx.x);
@@ -350,20 +352,25 @@ __global__ __launch_bounds__(BLOCK) void k_adj_fields(const float4* __restrict__
                                                        const float* __restrict__ LC, float* __restrict__ lam_out, KP k)
 {
     // the stencil cotangents of the tile and its rim from LDS windows
-    __shared__ float4 w0[SW], w1[SW];
-    const Tile t = this_tile(k);
+    constexpr int W = TileShape<STX, STY>::W;
+    __shared__ float4 w0[W], w1[W];
+    const Tile t = this_tile<STX, STY>(k);
     const Node& nd = t.nd;
     // batched staging (all loads before the LDS writes): 1.95 -> 1.73 ms per
     // adjoint step on the 128x128x512 jet
-    load_window<STY, true>(w0, AG0, k, t);
-    load_window<STY, true>(w1, AG1, k, t);
+    stage_window<STX, STY>(k, t, [&](int x, int y, int z) { return ldp(AG0, pidx(k, x, y, z)); },
+                           [&](int x, int y, int z) { return ldp(AG0, pidx(k, x, y, z)); },
+                           [&](int w, const float4& v) { w0[w] = v; });
+    stage_window<STX, STY>(k, t, [&](int x, int y, int z) { return ldp(AG1, pidx(k, x, y, z)); },
+                           [&](int x, int y, int z) { return ldp(AG1, pidx(k, x, y, z)); },
+                           [&](int w, const float4& v) { w1[w] = v; });
     __syncthreads();
     if (!nd.valid) return;
-    float Lphi = w0[wslot(t.lx, t.ly, 0, 0, 0)].w, Lrf = 0.f;
-    const float Lxr = w1[wslot(t.lx, t.ly, 0, 0, 0)].w;
+    float Lphi = w0[wslot<STX, STY>(t.lx, t.ly, 0, 0, 0)].w, Lrf = 0.f;
+    const float Lxr = w1[wslot<STX, STY>(t.lx, t.ly, 0, 0, 0)].w;
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
-        const int ws = wslot(t.lx, t.ly, -kCX[i], -kCY[i], -kCZ[i]);
+        const int ws = wslot<STX, STY>(t.lx, t.ly, -kCX[i], -kCY[i], -kCZ[i]);
         const float4 a0 = w0[ws], a1 = w1[ws];
         const float w3 = 3.f * wgt(i);
         Lphi += w3 * (kCX[i] * a0.x + kCY[i] * a0.y + kCZ[i] * a0.z);

@@ -115,12 +115,15 @@ template <int BC, class S>
 __global__ __launch_bounds__(BLOCK) void k_diag_init(const typename S::T* __restrict__ src,
                                                       const float* __restrict__ hprev, KP k, DiagWork w)
 {
-    const Node nd = this_node(k);
+    __shared__ float4 win[TileShape<STX, STY>::W];
+    const Tile t = this_tile<STX, STY>(k);
+    const Node& nd = t.nd;
+    stage_records<BC>(k, t, win);
     bool fg = false;
     if (nd.valid) {
         const uint32_t i = (uint32_t)nd.z * k.plane + nd.q;
         float d[Q], fr[Q], fb[Q];
-        read_state<BC, S>(src, k, hprev, nd, d, fr, fb);
+        read_state<BC, S>(src, k, hprev, t, win, d, fr, fb);
         double rr = 0.0, rb = 0.0;
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
