@@ -1022,11 +1022,12 @@ int diag_run(lbm_handle* h, void* work, lbm_jet_stats* stats, int64_t* volumes, 
             hipLaunchKernelGGL((q19::k19_diag_init<false, BC>), h->grid_all, dim3(BLOCK), 0, h->stream,
                                (const float*)cur_set(h).pop, hist, k, w);
         LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_diag_merge, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
+        hipLaunchKernelGGL(k_diag_merge, h->grid_all, dim3(BLOCK), 0, h->stream, k, w, h->q19);
         LAUNCH_CHECK();
         hipLaunchKernelGGL(k_diag_flatten, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_diag_count, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
+        hipLaunchKernelGGL(k_diag_count, dim3(h->grid_all.x, (unsigned)((h->p.nz + kCountPlanes - 1) / kCountPlanes)),
+                           dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();
         hipLaunchKernelGGL(k_diag_collect, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();

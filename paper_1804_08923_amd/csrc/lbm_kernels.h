@@ -1322,6 +1322,7 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
     const float4 rv = make_float4(xk, rec * gpx, rec * gpy, rec * gpz);
     st_rec<NT>(Rout, k, row, nd.x, rv);
     if (gcell) st_rec<NT>(Rout, k, grow, nd.x, mirror_rec(rv, 4));
+    end_block(k);
     const float nub9 = 9.f * nubf;
     // referenced 16-bit storage: reference record of this node, rounded as stored
     float rt = 0.f, uxt = 0.f, uyt = 0.f, uzt = 0.f, et = 0.f;
@@ -1329,6 +1330,7 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
         const uint4 qr = enc_ref<S>(rhof, uxf, uyf, uzf, (float)E1);
         st_rec<NT>(Qout, k, row, nd.x, qr);
         if (gcell) st_rec<NT>(Qout, k, grow, nd.x, mirror_ref(qr, 4));
+        end_block(k);
         const RefRec r = dec_ref<S>(qr);
         rt = r.rho;
         uxt = r.ux;
@@ -1365,6 +1367,9 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
     const float K1 = rhof * (3.f - 4.5f * u2);
     const float r45 = 4.5f * rhof;
     typename S::T down[9];  // the populations that leave downwards (slots 0..8)
+    // the order of one sum, written out for the same reason as end_block: which of the
+    // two terms is rounded by itself
+    constexpr bool kForceLast = sizeof(typename S::T) == 4 || S::kEqRef || BC == LBM_BC_PERIODIC;
 #pragma unroll
     for (int i = 1; i < Q; i += 2) {
         const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
@@ -1373,7 +1378,7 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
         const float cr = cx * grxf + cy * gryf + cz * grzf;
         const float cF = cx * Fxf + cy * Fyf + cz * Fzf;
         const float cg = cx * gpx + cy * gpy + cz * gpz;
-        const float t = r45 * cu + (nub9 * cr + 4.5f * cF);
+        const float t = r45 * cu + (kForceLast ? fmaf(4.5f, cF, nub9 * cr) : fmaf(nub9, cr, 4.5f * cF));
         const float even = w * (K0 + cu * t + (Aign * cg) * cg);
         const float odd = w * (cu * (K1 + r45 * (cu * cu)) + 1.5f * cF);
         // direction i (+c) and i + 1 (-c)
@@ -1612,6 +1617,83 @@ __global__ __launch_bounds__(BLOCK) void k_get_state(const typename S::T* __rest
     }
 }
 
+// FP64 sums over the directions of a shifted state: the mass m0 = rho - rho_b0, the
+// momentum and the kept colour's mass mk; marks has bit 0 set where every source
+// kept blue, bit 1 where any did.
+template <int I = 0>
+__device__ __forceinline__ void mass_dirs(const KP& k, const Tile& t, const float4* __restrict__ win, const float* d,
+                                          double& m0, double& mk, double (&j)[3], uint32_t& marks)
+{
+    if constexpr (I < Q) {
+        const float4 r = win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
+        const uint32_t bl = blue_kept(r.x);
+        const float f = d[I] + wgt(I) * k.rho_b0;
+        const float vt = I == 0 ? 0.f : (wgt(I) * inv_len(I)) * (kCX[I] * r.y + kCY[I] * r.z + kCZ[I] * r.w);
+        mk += (double)(r.x * f + (bl ? -vt : vt));
+        marks = (marks & (bl | 2u)) | (bl << 1);
+        m0 += (double)d[I];
+        if (kCX[I]) j[0] += kCX[I] * (double)d[I];
+        if (kCY[I]) j[1] += kCY[I] * (double)d[I];
+        if (kCZ[I]) j[2] += kCZ[I] * (double)d[I];
+        if (I % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+        mass_dirs<I + 1>(k, t, win, d, m0, mk, j, marks);
+    }
+}
+
+template <int I = 0>
+__device__ __forceinline__ void mixed_masses(const KP& k, const Tile& t, const float4* __restrict__ win, const float* d,
+                                             double& rr, double& rb)
+{
+    if constexpr (I < Q) {
+        float fr, fb;
+        colours_of<I>(k, d[I], win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], fr, fb);
+        rr += (double)fr;
+        rb += (double)fb;
+        if (I % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+        mixed_masses<I + 1>(k, t, win, d, rr, rb);
+    }
+}
+
+// Masses (m0 = rho - rho_b0, rho_r, rho_b) and momentum of a node in FP64.  Where all
+// sources kept the same colour, which is everywhere but next to phi = 0, its mass is
+// the sum of the kept values and the other colour the rest; else both colours are
+// rebuilt direction by direction.
+template <int BC, class S>
+__device__ __forceinline__ void node_masses(const typename S::T* __restrict__ src, const KP& k,
+                                            const float* __restrict__ hprev, const Tile& t,
+                                            const float4* __restrict__ win, double& m0, double& rr, double& rb,
+                                            double (&j)[3])
+{
+    m0 = rr = rb = j[0] = j[1] = j[2] = 0.0;
+    const Node& nd = t.nd;
+    if (!k.unshifted && !(BC == LBM_BC_JET && nd.z == k.nz - 1)) {
+        float d[Q], unused[Q];
+        double mk = 0.0;
+        uint32_t marks = 1u;
+        pull_dirs<BC, S, false>(src, k, nd.x, nd.y, nd.z, x_offsets<BC, typename S::T>(k, nd.x), d, unused, unused);
+        mass_dirs(k, t, win, d, m0, mk, j, marks);
+        const double other = (double)k.rho_b0 + m0 - mk;
+        rr = marks ? other : mk;
+        rb = marks ? mk : other;
+        if (marks == 2u) {  // mixed
+            rr = rb = 0.0;
+            mixed_masses(k, t, win, d, rr, rb);
+        }
+        return;
+    }
+    float d[Q], fr[Q], fb[Q];
+    read_state<BC, S>(src, k, hprev, t, win, d, fr, fb);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        m0 += (double)d[i];
+        rr += (double)fr[i];
+        rb += (double)fb[i];
+        if (kCX[i]) j[0] += kCX[i] * (double)d[i];
+        if (kCY[i]) j[1] += kCY[i] * (double)d[i];
+        if (kCZ[i]) j[2] += kCZ[i] * (double)d[i];
+    }
+}
+
 // macroscopic fields (node order) and FP64 audit partial sums (one slot per block)
 template <int BC, class S>
 __global__ __launch_bounds__(BLOCK) void k_macro(const typename S::T* __restrict__ src,
@@ -1625,20 +1707,10 @@ __global__ __launch_bounds__(BLOCK) void k_macro(const typename S::T* __restrict
     stage_records<BC>(k, t, win);
     double acc[5] = {0, 0, 0, 0, 0};
     if (nd.valid) {
-        float d[Q], fr[Q], fb[Q];
-        read_state<BC, S>(src, k, hprev, t, win, d, fr, fb);
-        double m0 = 0.0, rr = 0.0, rb = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            m0 += (double)d[i];
-            rr += (double)fr[i];
-            rb += (double)fb[i];
-            if (kCX[i]) jx += kCX[i] * (double)d[i];
-            if (kCY[i]) jy += kCY[i] * (double)d[i];
-            if (kCZ[i]) jz += kCZ[i] * (double)d[i];
-        }
+        double m0, rr, rb, j[3];
+        node_masses<BC, S>(src, k, hprev, t, win, m0, rr, rb, j);
         const double rho = (double)k.rho_b0 + m0;
-        const double px = jx + 0.5 * m0 * k.gx, py = jy + 0.5 * m0 * k.gy, pz = jz + 0.5 * m0 * k.gz;
+        const double px = j[0] + 0.5 * m0 * k.gx, py = j[1] + 0.5 * m0 * k.gy, pz = j[2] + 0.5 * m0 * k.gz;
         const size_t n = (size_t)nd.z * k.plane + nd.q;
         if (o_rr) o_rr[n] = (float)rr;
         if (o_rb) o_rb[n] = (float)rb;

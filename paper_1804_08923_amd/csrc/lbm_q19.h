@@ -597,8 +597,8 @@ __global__ __launch_bounds__(BLOCK) void k19_get_state(const float* __restrict__
 }
 
 // Jet diagnostics (Sec. IV C), first pass on D3Q19: the order parameter of the
-// current state binarised (phi as lbm_macroscopic returns it), labels and
-// counters; the union-find passes that follow are those of the D3Q27 path.
+// current state binarised (phi as lbm_macroscopic returns it) and labels; the
+// union-find passes that follow are those of the D3Q27 path.
 template <bool GEN, int BC>
 __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__ pop, const float* __restrict__ hist,
                                                        KP k, DiagWork w)
@@ -616,16 +616,11 @@ __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__
         }
         const double a = rr / k.rho_r0, b = rb / k.rho_b0;
         fg = (float)((a - b) / (a + b)) > 0.f;
-        w.label[s.n] = fg ? (int)s.n : -1;
-        w.count[s.n] = 0;
-        w.column[s.n] = 0;
     }
     const unsigned long long m = __ballot(fg);
-    const int zmax = wave_max_int(fg ? s.z : -1);
-    if ((threadIdx.x & 63) == 0 && m) {
-        atomicAdd(&w.hdr->jet_nodes, (unsigned long long)__popcll(m));
-        atomicMax(&w.hdr->front_z, zmax);
-    }
+    const int run = diag_run_label(m, s.x == 0, (int)s.n);
+    if (s.valid) w.label[s.n] = fg ? run : -1;
+    diag_tally(w, m, fg ? s.z : -1);
 }
 
 // general form of one node from FP64 colour populations: the deviations rounded
