@@ -50,4 +50,25 @@ __host__ __device__ constexpr int mirror_dir(int i, int m)
     return dir_of((m & 1) ? -kCX[i] : kCX[i], (m & 2) ? -kCY[i] : kCY[i], (m & 4) ? -kCZ[i] : kCZ[i]);
 }
 
+// c_i . (x, y, z) without the terms along which c_i vanishes: the compiler may not
+// drop a product with 0 by itself (24 to 72 instructions per wave in the step kernels)
+template <class T>
+__host__ __device__ __forceinline__ T cdot(int i, T x, T y, T z)
+{
+    const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
+    if (cx != 0) {
+        const T a = cx > 0 ? x : -x;
+        if (cy != 0) {
+            const T b = a + (cy > 0 ? y : -y);
+            return cz != 0 ? b + (cz > 0 ? z : -z) : b;
+        }
+        return cz != 0 ? a + (cz > 0 ? z : -z) : a;
+    }
+    if (cy != 0) {
+        const T b = cy > 0 ? y : -y;
+        return cz != 0 ? b + (cz > 0 ? z : -z) : b;
+    }
+    return cz != 0 ? (cz > 0 ? z : -z) : T(0);
+}
+
 }  // namespace cglbm
