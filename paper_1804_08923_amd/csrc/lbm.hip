@@ -75,12 +75,7 @@ namespace {
 uint64_t blocks_of(dim3 g) { return (uint64_t)g.x * g.y; }
 
 // partial sums of the FP64 audit: one slot per block of the macroscopic kernel
-// (stencil tiles; D3Q19: a flat grid)
-uint64_t audit_blocks(const lbm_params* p)
-{
-    const uint64_t plane = (uint64_t)p->nx * p->ny, flat = (plane + BLOCK - 1) / BLOCK;
-    return p->lattice == 19 ? flat * (uint64_t)p->nz : blocks_of(tile_grid<STX, STY>(p->nx, p->ny, p->nz));
-}
+uint64_t audit_blocks(const lbm_params* p) { return blocks_of(tile_grid<STX, STY>(p->nx, p->ny, p->nz)); }
 
 thread_local char g_err[512] = "";
 
@@ -124,6 +119,9 @@ uint64_t padded_nodes(const lbm_params* p)
 
 bool is_q19(const lbm_params* p) { return p->lattice == 19; }
 
+// rows of one set of populations and of every per-node array
+uint64_t row_count(const lbm_params* p) { return (uint64_t)p->ny * (p->nz + (p->bc == LBM_BC_JET ? 1 : 0)); }
+
 // Stride of a row of nx nodes: nx rounded up to the widest power of two of
 // elements, at most a 128-byte cache line, with which the rows fit the space of
 // the padded lattice that the buffer sizes state (a row of 27 slots per 27 padded
@@ -131,6 +129,14 @@ bool is_q19(const lbm_params* p) { return p->lattice == 19; }
 // lines; where nothing wider fits the stride is nx itself.
 int row_stride(const lbm_params* p)
 {
+    if (p->lattice == 19) {  // the buffer holds 39 floats per node, the shifted form takes 23
+        const uint64_t N = (uint64_t)p->nx * p->ny * p->nz, rows = row_count(p);
+        for (int a = 32; a > 1; a >>= 1) {
+            const int rs = (p->nx + a - 1) / a * a;
+            if (q19::rec_offset(rs * rows) + 16ull * rs * rows <= q19::pop_bytes(N)) return rs;
+        }
+        return p->nx;
+    }
     const uint64_t NP = padded_nodes(p), rows = (uint64_t)p->ny * (p->nz + (p->bc == LBM_BC_JET ? 1 : 0));
     for (int a = (int)(128 / elem_bytes(p->storage)); a > 1; a >>= 1) {
         const int rs = (p->nx + a - 1) / a * a;
@@ -139,8 +145,6 @@ int row_stride(const lbm_params* p)
     return p->nx;
 }
 
-// rows of one set of populations and of every per-node array
-uint64_t row_count(const lbm_params* p) { return (uint64_t)p->ny * (p->nz + (p->bc == LBM_BC_JET ? 1 : 0)); }
 
 int validate(const lbm_params* p)
 {
@@ -205,6 +209,7 @@ void fill_kp(const lbm_params* p, const float* inlet, KP* k)
     k->py = p->ny + 2;
     k->rs = row_stride(p);
     k->zg = p->bc == LBM_BC_JET ? 1 : 0;
+    k->n19 = is_q19(p) ? (uint32_t)(row_count(p) * (uint64_t)k->rs) : 0u;
     k->NP = (uint32_t)padded_nodes(p);
     k->plane = (uint32_t)p->nx * (uint32_t)p->ny;
     k->N = k->plane * (uint32_t)p->nz;
@@ -481,7 +486,7 @@ int lbm_init(lbm_handle** h, const lbm_params* p, const lbm_buffers* buf, const 
     H->nblk = (int)(H->grid_all.x * H->grid_all.y);
     H->naud = (int)audit_blocks(p);
     const SnapBytes sb = snap_bytes_of(p);
-    H->nt = (uint64_t)sb.pop + sb.rec > kCacheBytes;
+    H->nt = (H->q19 ? 92ull * H->k.n19 : (uint64_t)sb.pop + sb.rec) > kCacheBytes;
     if (H->q19) {
         H->F2 = (float2*)buf->fields;
         H->PD = nullptr;
@@ -526,40 +531,36 @@ namespace {
 
 // One full time step from the current state into the state set dst, which
 // becomes the current state.
-template <int BC>
+template <int BC, bool GEN>
 int q19_launch(lbm_handle* h, const StateSet& dst_set, hipEvent_t* e)
 {
     const KP k = read_kp(h);
     const float* src = (const float*)cur_set(h).pop;
     float* dst = (float*)dst_set.pop;
-    const float* hprev = cur_set(h).hist;
-    float* hcur = dst_set.hist;
-    // jet: the outlet plane by its own kernel, then the planes below it
-    const dim3 gd = BC == LBM_BC_JET ? dim3(h->grid_all.x, (unsigned)(h->p.nz - 1)) : h->grid_all;
+    KP kd = k;
+    // jet: the outlet plane (and the inlet cells) by its own kernel, then the planes below it
     if (BC == LBM_BC_JET) {
-        if (h->unshifted)
-            hipLaunchKernelGGL(q19::k19_outlet<true>, h->grid_plane, dim3(BLOCK), 0, h->stream, src, h->F2, hprev,
-                               hcur, k);
-        else
-            hipLaunchKernelGGL(q19::k19_outlet<false>, h->grid_plane, dim3(BLOCK), 0, h->stream, src, h->F2, hprev,
-                               hcur, k);
+        hipLaunchKernelGGL(q19::k19_outlet<GEN>, h->grid_rows, dim3(OBLOCK), 0, h->stream, src, h->F2,
+                           cur_set(h).hist, dst_set.hist, dst, k);
         LAUNCH_CHECK();
+        kd.planes -= 1;
     }
     if (e) HIP_CHECK(hipEventRecord(e[1], h->stream));
-    if (h->unshifted)
-        hipLaunchKernelGGL((q19::k19_density<true, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
-    else
-        hipLaunchKernelGGL((q19::k19_density<false, BC>), gd, dim3(BLOCK), 0, h->stream, src, h->F2, k);
-    LAUNCH_CHECK();
-    if (e) HIP_CHECK(hipEventRecord(e[2], h->stream));
-    if (h->unshifted)
-        hipLaunchKernelGGL((q19::k19_collide<true, BC>), h->grid_all, dim3(BLOCK), 0, h->stream, src, dst, h->F2,
-                           hcur, k);
-    else
-        hipLaunchKernelGGL((q19::k19_collide<false, BC>), h->grid_all, dim3(BLOCK), 0, h->stream, src, dst, h->F2,
-                           hcur, k);
-    LAUNCH_CHECK();
-    return LBM_OK;
+    return with_tiles<StF32>(h->tiles, [&](auto tl) -> int {
+        using TL = decltype(tl);
+        hipLaunchKernelGGL((q19::k19_density<GEN, BC, TL>), h->grid_dtiles, dim3(TL::DX * TL::DY), 0, h->stream, src,
+                           h->F2, kd);
+        LAUNCH_CHECK();
+        if (e) HIP_CHECK(hipEventRecord(e[2], h->stream));
+        if (h->nt)
+            hipLaunchKernelGGL((q19::k19_collide<GEN, BC, TL, true>), h->grid_ctiles, dim3(BLOCK), 0, h->stream, src,
+                               dst, h->F2, dst_set.hist, k, q19::consts_of(k));
+        else
+            hipLaunchKernelGGL((q19::k19_collide<GEN, BC, TL, false>), h->grid_ctiles, dim3(BLOCK), 0, h->stream, src,
+                               dst, h->F2, dst_set.hist, k, q19::consts_of(k));
+        LAUNCH_CHECK();
+        return LBM_OK;
+    });
 }
 
 int q19_step(lbm_handle* h, const StateSet& dst_set, int dst_cs)
@@ -575,8 +576,11 @@ int q19_step(lbm_handle* h, const StateSet& dst_set, int dst_cs)
         h->ev_used += 4;
         HIP_CHECK(hipEventRecord(e[0], h->stream));
     }
-    const int rc = h->p.bc == LBM_BC_JET ? q19_launch<LBM_BC_JET>(h, dst_set, e)
-                                         : q19_launch<LBM_BC_PERIODIC>(h, dst_set, e);
+    const bool jet = h->p.bc == LBM_BC_JET;
+    const int rc = h->unshifted ? (jet ? q19_launch<LBM_BC_JET, true>(h, dst_set, e)
+                                       : q19_launch<LBM_BC_PERIODIC, true>(h, dst_set, e))
+                                : (jet ? q19_launch<LBM_BC_JET, false>(h, dst_set, e)
+                                       : q19_launch<LBM_BC_PERIODIC, false>(h, dst_set, e));
     if (rc != LBM_OK) return rc;
     if (e) HIP_CHECK(hipEventRecord(e[3], h->stream));
     h->cs = dst_cs;
@@ -736,13 +740,13 @@ int lbm_macroscopic(lbm_handle* h, float* rho_r, float* rho_b, float* u, float* 
         double* part = audit ? h->audit : nullptr;
         const bool jet = h->p.bc == LBM_BC_JET;
         if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_macro<true, LBM_BC_PERIODIC>), h->grid_all, dim3(BLOCK), 0, h->stream, pop,
+            hipLaunchKernelGGL((q19::k19_macro<true, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
                                hist, k, rho_r, rho_b, u, phi, part);
         else if (jet)
-            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_JET>), h->grid_all, dim3(BLOCK), 0, h->stream, pop, hist,
+            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_JET>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop, hist,
                                k, rho_r, rho_b, u, phi, part);
         else
-            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_PERIODIC>), h->grid_all, dim3(BLOCK), 0, h->stream, pop,
+            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
                                hist, k, rho_r, rho_b, u, phi, part);
         LAUNCH_CHECK();
         return LBM_OK;
@@ -775,13 +779,13 @@ int lbm_get_state(lbm_handle* h, float* state)
         const float* pop = (const float*)cur_set(h).pop;
         const float* hist = cur_set(h).hist;
         if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_get_state<true, LBM_BC_PERIODIC>), h->grid_all, dim3(BLOCK), 0, h->stream,
+            hipLaunchKernelGGL((q19::k19_get_state<true, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                pop, hist, k, state);
         else if (h->p.bc == LBM_BC_JET)
-            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_JET>), h->grid_all, dim3(BLOCK), 0, h->stream, pop,
+            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_JET>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
                                hist, k, state);
         else
-            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_PERIODIC>), h->grid_all, dim3(BLOCK), 0, h->stream,
+            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                pop, hist, k, state);
         LAUNCH_CHECK();
         return LBM_OK;
@@ -1016,13 +1020,13 @@ int diag_run(lbm_handle* h, void* work, lbm_jet_stats* stats, int64_t* volumes, 
             hipLaunchKernelGGL((k_diag_init<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                (const typename S::T*)cur_set(h).pop, hist, k, w);
         else if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_diag_init<true, BC>), h->grid_all, dim3(BLOCK), 0, h->stream,
+            hipLaunchKernelGGL((q19::k19_diag_init<true, BC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                (const float*)cur_set(h).pop, hist, k, w);
         else
-            hipLaunchKernelGGL((q19::k19_diag_init<false, BC>), h->grid_all, dim3(BLOCK), 0, h->stream,
+            hipLaunchKernelGGL((q19::k19_diag_init<false, BC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
                                (const float*)cur_set(h).pop, hist, k, w);
         LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_diag_merge, h->grid_all, dim3(BLOCK), 0, h->stream, k, w, h->q19);
+        hipLaunchKernelGGL(k_diag_merge, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();
         hipLaunchKernelGGL(k_diag_flatten, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();

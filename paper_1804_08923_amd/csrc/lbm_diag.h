@@ -115,15 +115,13 @@ __global__ void k_diag_clear(DiagWork w)
 }
 
 // Label of a jet node on entry to the merge: the first node of its run along x
-// within the wavefront's segment (lane 0, or a row start, begins a segment), so
-// that the runs need no union-find.  fg: lane mask of the jet nodes, i its index.
-__device__ __forceinline__ int diag_run_label(unsigned long long fg, bool row_start, int i)
+// within the wavefront's 64 nodes of a row, so that the runs need no union-find.
+// fg: lane mask of the jet nodes, i the node's index.
+__device__ __forceinline__ int diag_run_label(unsigned long long fg, int i)
 {
     const int lane = (int)threadIdx.x & 63;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const unsigned long long gap = ~fg & below, rows = __ballot(row_start) & (below | (1ull << lane));
-    const int after_gap = gap ? 64 - __clzll(gap) : 0, row = rows ? 63 - __clzll(rows) : 0;
-    return i - (lane - max(after_gap, row));
+    const unsigned long long gap = ~fg & ((1ull << lane) - 1ull);
+    return i - (lane - (gap ? 64 - __clzll(gap) : 0));
 }
 
 // jet nodes and leading edge of a wavefront into the header
@@ -157,7 +155,7 @@ __global__ __launch_bounds__(BLOCK) void k_diag_init(const typename S::T* __rest
             float d[Q], unused[Q], m0 = 0.f, x0 = 0.f, cf = 0.f, cv = 0.f;
             uint32_t bl = 0;
             pull_dirs<BC, S, false>(src, k, nd.x, nd.y, nd.z, x_offsets<BC, typename S::T>(k, nd.x), d, unused, unused);
-            accum_density_win<STX, STY>(k, d, win, t.lx, t.ly, m0, x0, bl, cf, cv);
+            accum_density_win<STX, STY, false>(k, d, win, t.lx, t.ly, m0, x0, bl, cf, cv);
             const float rho = k.rho_b0 + m0, mk = x0 * rho + (cf + (bl ? -cv : cv));
             const float a = (bl ? rho - mk : mk) * k.rho_b0, b = (bl ? mk : rho - mk) * k.rho_r0;
             sure = fabsf(a - b) > 1e-3f * (a + b) && a + b > 0.f;
@@ -171,26 +169,24 @@ __global__ __launch_bounds__(BLOCK) void k_diag_init(const typename S::T* __rest
         }
     }
     const unsigned long long m = __ballot(fg);
-    const int run = diag_run_label(m, nd.x == 0, i);
+    const int run = diag_run_label(m, i);
     if (nd.valid) w.label[i] = fg ? run : -1;
     diag_tally(w, m, fg ? nd.z : -1);
 }
 
 // 2. union with the face neighbours at -x, -y, -z.  Runs are joined where segments
-// meet (flat: segments of 64 nodes of the plane index, else of x); towards -y and -z
-// one union is enough for nodes whose runs go on side by side.
-__global__ __launch_bounds__(BLOCK) void k_diag_merge(KP k, DiagWork w, int flat)
+// meet; towards -y and -z one union is enough for nodes whose runs go on side by
+// side.
+__global__ __launch_bounds__(BLOCK) void k_diag_merge(KP k, DiagWork w)
 {
     const Node nd = this_node(k);
     if (!nd.valid) return;
     const int i = (int)((uint32_t)nd.z * k.plane + nd.q);
     if (diag_load(w.label + i) < 0) return;
     const int walk = (int)k.N;
-    const bool begins = ((flat ? (int)nd.q : nd.x) & 63) == 0;
+    const bool begins = (nd.x & 63) == 0;
     const bool left = nd.x > 0 && w.label[i - 1] >= 0;
     if (left && begins) diag_unite(w.label, i, i - 1, walk, &w.hdr->overflow);
-    // (a row below may be cut into other segments where flat: the neighbours' own
-    // unions join those)
     const auto join = [&](int o) {
         if (w.label[i - o] < 0) return;
         if (left && !begins && w.label[i - o - 1] >= 0) return;  // the node to the left joins the same two runs

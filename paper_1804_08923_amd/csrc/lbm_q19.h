@@ -13,9 +13,12 @@
 //                relaxed with s0, s1, s2nu, s2b, s3, s4 (Eq. scoll).
 // Periodic and jet lattices, FP32 storage; the arithmetic is FP64 (the kernels are
 // bound by memory traffic, and FP32 arithmetic would add about 1e-5 of the
-// spurious velocity of a resting droplet to the FP32 storage floor).  Node
-// index n = (z ny + y) nx + x with no padding; the periodic wrap is taken on
-// the index.
+// spurious velocity of a resting droplet to the FP32 storage floor).
+// Layout, tiles, windows and walls are those of the D3Q27 kernels (rows without
+// x ghosts, a wavefront inside one row, the jet's ghost plane z = -1): against
+// per-thread wrapped indices and neighbours through the caches the step on the
+// 128x128x512 jet went from 0.61 to 0.46 ms.  The collision is bound by
+// its FP64 instructions (980 -> 550 per wave by pairs of opposite directions).
 //
 // Reduced collision.  With the paper's rates (s0 = s1 = 0, s2b = s3 = s4 = 1)
 // the GMRT collision plus forcing, f - T^-1 K T (f - feq) + T^-1 (I - K/2) T F'
@@ -29,15 +32,16 @@
 // nonzero and each <= 2 form a set closed under the shift), and the raw
 // monomial moments give the populations in closed form on D3Q19.
 //
-// Two state forms share one buffer of N-float planes:
-//   general  planes 0..18 the colour-blind deviations d_i = f_i - w_i rho_b0
+// Two state forms share one buffer:
+//   general  planes of N floats in node order (z ny + y) nx + x: planes 0..18 the
+//            colour-blind deviations d_i = f_i - w_i rho_b0
 //            after streaming at x, 19..37 the populations of the node's
 //            minority colour, 38 its tag (0: red, 1: blue); the majority colour
 //            is f_i minus the minority one (written by init and set_state, read
 //            by the first step);
-//   shifted  planes 0..18 the deviations d_i = fdag_i - w_i rho_b0 at the node
-//            that produced them, then (from byte align256(76 N)) four planes
-//            of the record (x, V_x, V_y, V_z) per node, V = beta (rho_r rho_b / rho)
+//   shifted  rows of the deviations d_i = fdag_i - w_i rho_b0 at the node
+//            that produced them, direction i of row r at (r 19 + slot19(i)) rs + x,
+//            then the records (x, V_x, V_y, V_z) of the nodes, V = beta (rho_r rho_b / rho)
 //            (1 - alpha_bar) grad phi / |grad phi|: the red population pulled
 //            from x - c_i is (rho_r / rho) f_i + varphi-weighted c_i . V (Eqs.
 //            op3r/op3b), so both colours are rebuilt from 23 floats.  x holds
@@ -67,8 +71,8 @@ __host__ __device__ constexpr double krec(int i)
     return csq(i) == 1 ? 1.0 / 12.0 : 0.029462782549439480;  // 1 / (24 sqrt 2)
 }
 
-// byte offset of the records in the shifted form
-__host__ __device__ inline uint64_t rec_offset(uint64_t N) { return (76ull * N + 255ull) & ~255ull; }
+// byte offset of the records of a shifted form with n = rows x stride nodes
+__host__ __device__ inline uint64_t rec_offset(uint64_t n) { return (76ull * n + 255ull) & ~255ull; }
 
 // buffer bytes: the larger of the two forms
 __host__ inline uint64_t pop_bytes(uint64_t N)
@@ -77,74 +81,32 @@ __host__ inline uint64_t pop_bytes(uint64_t N)
     return general > shifted ? general : shifted;
 }
 
-// This thread's node and the wrapped neighbour coordinates.  Blocks are handed
-// to the 8 XCDs round-robin (block b of a plane goes to XCD b mod 8 when a
-// plane has a multiple of 8 blocks); the plane's blocks are permuted so that
-// each XCD takes a contiguous band of them, whose y- and z-neighbour rows are
-// then fetched into that XCD's L2 only, instead of into three.
-constexpr uint32_t kXcds = 8;
-
-struct Site {
-    uint32_t n;                    // node index
-    uint32_t q;                    // y nx + x
-    int x, y, z;
-    uint32_t xs[3], ys[3], zs[3];  // periodic: x - 1, x, x + 1; (y - 1, y, y + 1) nx; (z - 1, z, z + 1) nx ny
-    bool valid;
-};
-
-__device__ __forceinline__ Site site(const KP& k, int zoff = 0)
+// Slot of direction i within its row: the directions of a group (c_y, c_z) follow
+// one another in the order of c_x; groups 00, -0, +0, 0-, 0+ of three, then --, +-,
+// -+, ++ of one.
+__host__ __device__ constexpr int slot19(int i)
 {
-    Site s;
-    const uint32_t B = gridDim.x, b = blockIdx.x;
-    const uint32_t pb = (B % kXcds == 0) ? (b % kXcds) * (B / kXcds) + b / kXcds : b;
-    const uint32_t p = pb * (uint32_t)BLOCK + threadIdx.x;
-    s.valid = p < k.plane;
-    const int z = (int)blockIdx.y + zoff;
-    const int y = (int)(((uint64_t)p * k.nx_mul) >> k.nx_sh);
-    const int x = (int)p - y * k.nx;
-    s.xs[0] = x == 0 ? k.nx - 1 : x - 1;
-    s.xs[1] = x;
-    s.xs[2] = x == k.nx - 1 ? 0 : x + 1;
-    s.ys[0] = (uint32_t)(y == 0 ? k.ny - 1 : y - 1) * k.nx;
-    s.ys[1] = (uint32_t)y * k.nx;
-    s.ys[2] = (uint32_t)(y == k.ny - 1 ? 0 : y + 1) * k.nx;
-    s.zs[0] = (uint32_t)(z == 0 ? k.nz - 1 : z - 1) * k.plane;
-    s.zs[1] = (uint32_t)z * k.plane;
-    s.zs[2] = (uint32_t)(z == k.nz - 1 ? 0 : z + 1) * k.plane;
-    s.n = s.zs[1] + p;
-    s.q = p;
-    s.x = x;
-    s.y = y;
-    s.z = z;
-    return s;
+    const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
+    if (cy != 0 && cz != 0) return 15 + (cy > 0 ? 1 : 0) + (cz > 0 ? 2 : 0);
+    return (cy < 0 ? 3 : cy > 0 ? 6 : cz < 0 ? 9 : cz > 0 ? 12 : 0) + cx + 1;
 }
 
-// node at offset (dx, dy, dz) in {-1, 0, 1}^3
-__device__ __forceinline__ uint32_t at(const Site& s, int dx, int dy, int dz)
+// the records (x, V) of the shifted form
+__device__ __forceinline__ const float4* records(const float* pop, const KP& k)
 {
-    return s.zs[dz + 1] + s.ys[dy + 1] + s.xs[dx + 1];
+    return (const float4*)((const char*)pop + rec_offset(k.n19));
 }
 
-// the recolouring record of the shifted form: four planes of N floats, the
-// minority fraction x, then V_x, V_y, V_z
-__device__ __forceinline__ const float* records(const float* pop, uint64_t N)
+// red part of a population of value f pulled along lattice direction i from a node
+// with record r (mirrored at walls)
+__device__ __forceinline__ double red_part(const float4& r, int i, double f)
 {
-    return (const float*)((const char*)pop + rec_offset(N));
-}
-
-// red part of a population of value f pulled from node src along lattice
-// direction i (whose velocity, reflected at walls, is (ex, ey, ez)): only the
-// V components along which c_i is nonzero are read
-__device__ __forceinline__ double red_part(const float* __restrict__ R, size_t N, uint32_t src, int i, double f,
-                                           double ex, double ey, double ez)
-{
-    const float x = R[src];
     double cv = 0.0;
-    if (kCX[i]) cv += ex * (double)R[N + src];
-    if (kCY[i]) cv += ey * (double)R[2 * N + src];
-    if (kCZ[i]) cv += ez * (double)R[3 * N + src];
+    if (kCX[i]) cv += kCX[i] * (double)r.y;
+    if (kCY[i]) cv += kCY[i] * (double)r.z;
+    if (kCZ[i]) cv += kCZ[i] * (double)r.w;
     const double rec = i ? krec(i) * cv : 0.0;
-    return signbit(x) ? f - (-(double)x * f - rec) : (double)x * f + rec;
+    return signbit(r.x) ? f - (-(double)r.x * f - rec) : (double)r.x * f + rec;
 }
 
 // Jet boundaries (Sec. IV A), with the rules the D3Q27 path uses: a circular
@@ -173,50 +135,29 @@ __device__ __forceinline__ double inlet_feq19(const KP& k, int i, int xg, int yg
     return (double)k.rho_r0 * (ph + w19(i) * poly);
 }
 
-// colour of population j of the shifted form at node src (Eqs. op3r/op3b)
-__device__ __forceinline__ void shifted_pop(const float* __restrict__ pop, const KP& k, int j, uint32_t src,
-                                            double& d, double& fr)
+// Deviation of direction I streamed into node (x, y, z) of the shifted form, row
+// uniform (offsets xo of x).  Not for the jet's outlet plane, which the convective
+// rule fills.
+template <int BC, int I>
+__device__ __forceinline__ float pull19(const float* __restrict__ pop, const KP& k, int y, int z, const XOff& xo)
 {
-    const size_t N = k.N;
-    d = (double)pop[(size_t)j * N + src];
-    fr = red_part(records(pop, N), N, src, j, d + w19(j) * k.rho_b0, kCX[j], kCY[j], kCZ[j]);
+    constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
+    // first of the three slots that the offsets count from
+    constexpr int base = slot19(I) - cx - 1, mbase = slot19(mirror_dir(I, 2)) - cx - 1;
+    bool my;
+    const uint32_t row = group_row<BC, cy, cz>(k, y, z, my);
+    const uint32_t rs = (uint32_t)k.rs;
+    const auto r = row_rsrc(pop + (size_t)row * (Q19 * rs) + (uint32_t)(my ? mbase : base) * rs, 3u * rs);
+    return ld_row<float>(r, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o), 0u);
 }
 
-// Population i streamed into node (x, y, z) of the shifted form: its deviation
-// d and its red part fr (the blue part is d + w_i rho_b0 - fr).  Not for the
-// jet's outlet plane, which the convective rule fills.
-// BOT: the node may lie on the bottom plane z = 0 (the only plane that sees
-// the inlet and the bottom wall); false lets the compiler drop that code
-template <int BC, bool BOT = true>
-__device__ __forceinline__ void pull_at(const float* __restrict__ pop, const KP& k, const Site& s, int i, double& d,
-                                        double& fr)
+template <int BC, int I = 0>
+__device__ __forceinline__ void pull_all19(const float* __restrict__ pop, const KP& k, int y, int z, const XOff& xo,
+                                           float* d)
 {
-    if constexpr (BC == LBM_BC_PERIODIC) {
-        shifted_pop(pop, k, i, at(s, -kCX[i], -kCY[i], -kCZ[i]), d, fr);
-    } else {
-        const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
-        // the source x - c_i lies outside along an axis: reflect there (the
-        // walls act per axis; selects, no branch, so the loads of the 19
-        // directions issue together)
-        const bool ox = cx > 0 ? s.x == 0 : (cx < 0 ? s.x == k.nx - 1 : false);
-        const bool oy = cy > 0 ? s.y == 0 : (cy < 0 ? s.y == k.ny - 1 : false);
-        const bool oz = BOT && cz > 0 && s.z == 0;
-        if (BOT && oz && inlet_inside(k, s.x - cx, s.y - cy)) {  // only on the bottom plane
-            fr = inlet_feq19(k, i, s.x - cx, s.y - cy, k.t - 1);  // left the inlet at the previous time level
-            d = fr - w19(i) * k.rho_b0;
-            return;
-        }
-        const int m = (ox ? 1 : 0) | (oy ? 2 : 0) | (oz ? 4 : 0);
-        const int j = m == 0 ? i : m == 1 ? mirror_dir(i, 1) : m == 2 ? mirror_dir(i, 2) : m == 3 ? mirror_dir(i, 3)
-                    : m == 4 ? mirror_dir(i, 4) : m == 5 ? mirror_dir(i, 5) : m == 6 ? mirror_dir(i, 6)
-                    : mirror_dir(i, 7);
-        const int off = (ox ? 0 : cx) + (oy ? 0 : cy) * k.nx + (oz ? 0 : cz) * (int)k.plane;
-        const uint32_t src = (uint32_t)((int)s.n - off);
-        const size_t N = k.N;
-        d = (double)pop[(size_t)j * N + src];
-        // c_j: the components of c_i, reversed along the reflecting axes
-        fr = red_part(records(pop, N), N, src, i, d + w19(i) * k.rho_b0, ox ? -cx : cx, oy ? -cy : cy,
-                      oz ? -cz : cz);
+    if constexpr (I < Q19) {
+        d[I] = pull19<BC, I>(pop, k, y, z, xo);
+        pull_all19<BC, I + 1>(pop, k, y, z, xo, d);
     }
 }
 
@@ -235,16 +176,25 @@ __device__ __forceinline__ void general_pop(const float* __restrict__ pop, const
 // f(N, t) = [f(N, t - 1) + lam f(N - 1, t)] / (1 + lam), lam = max(0, u_z(N - 1, t))
 // with u_z of the freshly streamed plane below (half-force term included);
 // hist holds f(N, t - 1) as (d, fr) planes.  Both colours.
-__device__ __forceinline__ void outlet_rule(const float* __restrict__ pop, const float* __restrict__ hist,
-                                            const KP& k, const Site& s, double (&d)[Q19], double (&fr)[Q19])
+template <int I = 0>
+__device__ __forceinline__ void below_dirs(const float* __restrict__ pop, const KP& k, const Node& nd, const XOff& xo,
+                                           double (&d)[Q19], double (&fr)[Q19])
 {
-    Site below = s;  // the plane under the outlet
-    below.z = k.nz - 2;
-    below.n = s.n - k.plane;
+    if constexpr (I < Q19) {
+        int m;
+        const float4 r = pull_rec<LBM_BC_JET, I>(records(pop, k), k, nd.y, k.nz - 2, xo, m);
+        d[I] = (double)pull19<LBM_BC_JET, I>(pop, k, nd.y, k.nz - 2, xo);
+        fr[I] = red_part(mirror_rec(r, m), I, d[I] + w19(I) * k.rho_b0);
+        below_dirs<I + 1>(pop, k, nd, xo, d, fr);
+    }
+}
+__device__ __forceinline__ void outlet_rule(const float* __restrict__ pop, const float* __restrict__ hist,
+                                            const KP& k, const Node& nd, double (&d)[Q19], double (&fr)[Q19])
+{
+    below_dirs(pop, k, nd, x_offsets<LBM_BC_JET, float>(k, nd.x), d, fr);
     double m = 0.0, jz = 0.0;
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
-        pull_at<LBM_BC_JET, false>(pop, k, below, i, d[i], fr[i]);
         m += d[i];
         if (kCZ[i]) jz += kCZ[i] * d[i];
     }
@@ -253,25 +203,50 @@ __device__ __forceinline__ void outlet_rule(const float* __restrict__ pop, const
     const size_t P = k.plane;
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
-        d[i] = ((double)hist[(size_t)i * P + s.q] + lam * d[i]) * il;
-        fr[i] = ((double)hist[(size_t)(Q19 + i) * P + s.q] + lam * fr[i]) * il;
+        d[i] = ((double)hist[(size_t)i * P + nd.q] + lam * d[i]) * il;
+        fr[i] = ((double)hist[(size_t)(Q19 + i) * P + nd.q] + lam * fr[i]) * il;
     }
 }
 
-// The state at this node: the populations after streaming, (d_i, fr_i), of
-// either form; the jet's outlet plane from the general form, or by the rule.
+// the records of a tile and its rim into LDS
+template <int BC, int TX, int TY>
+__device__ __forceinline__ void stage_records19(const float* __restrict__ pop, const KP& k, const Tile& t,
+                                                float4* __restrict__ win)
+{
+    const float4* R = records(pop, k);
+    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return rec_at<BC, true>(k, R, x, y, z); },
+                         [&](int x, int y, int z) { return rec_at<BC>(k, R, x, y, z); },
+                         [&](int w, const float4& v) { win[w] = v; });
+}
+
+// node order index
+__device__ __forceinline__ uint32_t order_of(const KP& k, const Node& nd) { return (uint32_t)nd.z * k.plane + nd.q; }
+
+// The state at a node of the tile: the populations after streaming, (d_i, fr_i), of
+// either form; the jet's outlet plane from the general form, or by the rule.  The
+// records are in the window (shifted form).
+template <int BC, int I = 0>
+__device__ __forceinline__ void window_dirs(const float* __restrict__ pop, const KP& k, const Tile& t, const XOff& xo,
+                                            const float4* __restrict__ win, double (&d)[Q19], double (&fr)[Q19])
+{
+    if constexpr (I < Q19) {
+        d[I] = (double)pull19<BC, I>(pop, k, t.nd.y, t.nd.z, xo);
+        fr[I] = red_part(win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], I, d[I] + w19(I) * k.rho_b0);
+        window_dirs<BC, I + 1>(pop, k, t, xo, win, d, fr);
+    }
+}
 template <bool GEN, int BC>
 __device__ __forceinline__ void node_state(const float* __restrict__ pop, const float* __restrict__ hist, const KP& k,
-                                           const Site& s, double (&d)[Q19], double (&fr)[Q19])
+                                           const Tile& t, const float4* __restrict__ win, double (&d)[Q19],
+                                           double (&fr)[Q19])
 {
     if (GEN) {
 #pragma unroll
-        for (int i = 0; i < Q19; ++i) general_pop(pop, k, s.n, i, d[i], fr[i]);
-    } else if (BC == LBM_BC_JET && s.z == k.nz - 1) {
-        outlet_rule(pop, hist, k, s, d, fr);
+        for (int i = 0; i < Q19; ++i) general_pop(pop, k, order_of(k, t.nd), i, d[i], fr[i]);
+    } else if (BC == LBM_BC_JET && t.nd.z == k.nz - 1) {
+        outlet_rule(pop, hist, k, t.nd, d, fr);
     } else {
-#pragma unroll
-        for (int i = 0; i < Q19; ++i) pull_at<BC>(pop, k, s, i, d[i], fr[i]);
+        window_dirs<BC>(pop, k, t, x_offsets<BC, float>(k, t.nd.x), win, d, fr);
     }
 }
 
@@ -281,55 +256,82 @@ __device__ __forceinline__ void node_state(const float* __restrict__ pop, const 
 __device__ __forceinline__ void store_fields(float2* __restrict__ F, const KP& k, uint32_t n, double rr, double rb,
                                              double m)
 {
-    const double a = rr / k.rho_r0, b = rb / k.rho_b0;
-    F[n] = make_float2((float)((a - b) / (a + b)), (float)m);
-    F[(size_t)k.N + n] = make_float2((float)rr, (float)rb);
+    // both quotients scaled by rho_r0 rho_b0: one division
+    const double a = rr * (double)k.rho_b0, b = rb * (double)k.rho_r0;
+    stp(F, n, make_float2((float)div_fields(a - b, a + b), (float)m));
+    stp(F + k.N, n, make_float2((float)rr, (float)rb));
 }
 
-template <bool GEN, int BC, bool BOT>
-__device__ __forceinline__ void density_sums(const float* __restrict__ pop, const KP& k, const Site& s, double& rr,
-                                             double& rb, double& m)
+template <int BC, int TX, int TY, int I = 0>
+__device__ __forceinline__ void density_dirs(const float* d, const KP& k, const Tile& t, const float4* __restrict__ win,
+                                             double& rr, double& rb, double& m)
 {
-#pragma unroll
-    for (int i = 0; i < Q19; ++i) {
-        double d, fr;
-        if (GEN)
-            general_pop(pop, k, s.n, i, d, fr);
-        else
-            pull_at<BC, BOT>(pop, k, s, i, d, fr);
-        m += d;
+    if constexpr (I < Q19) {
+        const double f = (double)d[I] + w19(I) * k.rho_b0;
+        const double fr = red_part(win[wslot<TX, TY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], I, f);
+        m += (double)d[I];
         rr += fr;
-        rb += d + w19(i) * k.rho_b0 - fr;
+        rb += f - fr;
+        density_dirs<BC, TX, TY, I + 1>(d, k, t, win, rr, rb, m);
     }
 }
 
 // Density pass (Eq. order): the fields F of every node, on the
 // planes below the jet's outlet (all planes when periodic).
-template <bool GEN, int BC>
-__global__ __launch_bounds__(BLOCK) void k19_density(const float* __restrict__ pop, float2* __restrict__ F, KP k)
+template <bool GEN, int BC, class TL>
+__global__ __launch_bounds__(TL::DX* TL::DY) void k19_density(const float* __restrict__ pop, float2* __restrict__ F,
+                                                              KP k)
 {
-    const Site s = site(k);
-    if (!s.valid) return;
+    constexpr int TX = TL::DX, TY = TL::DY;
+    __shared__ float4 win[GEN ? 1 : TileShape<TX, TY>::W];
+    const Tile t = this_tile<TX, TY>(k);
     double rr = 0.0, rb = 0.0, m = 0.0;
-    if (BC == LBM_BC_JET && s.z == 0)  // block-uniform
-        density_sums<GEN, BC, true>(pop, k, s, rr, rb, m);
-    else
-        density_sums<GEN, BC, false>(pop, k, s, rr, rb, m);
-    store_fields(F, k, s.n, rr, rb, m);
+    if (!GEN) {
+        stage_records19<BC, TX, TY>(pop, k, t, win);
+        __syncthreads();
+    }
+    if (!t.nd.valid) return;
+    if (GEN) {
+#pragma unroll
+        for (int i = 0; i < Q19; ++i) {
+            double d, fr;
+            general_pop(pop, k, order_of(k, t.nd), i, d, fr);
+            m += d;
+            rr += fr;
+            rb += d + w19(i) * k.rho_b0 - fr;
+        }
+    } else {
+        float d[Q19];
+        pull_all19<BC>(pop, k, t.nd.y, t.nd.z, x_offsets<BC, float>(k, t.nd.x), d);
+        density_dirs<BC, TX, TY>(d, k, t, win, rr, rb, m);
+    }
+    store_fields(F, k, order_of(k, t.nd), rr, rb, m);
 }
 
-// The jet's outlet plane (one plane, blockIdx.y = 0): its populations after
+// The jet's outlet plane (grid: row segments of OBLOCK nodes): its populations after
 // streaming (general form, or the convective rule from hprev) go to hcur as
 // (d, fr), where the collision and the next step's rule read them, and its
-// fields to F.
+// fields to F.  Also the inlet cells of the ghost plane of the state that the step
+// writes (the red equilibrium at this time level, rounded to FP32 like every stored
+// population, and a pure red record).
 template <bool GEN>
-__global__ __launch_bounds__(BLOCK) void k19_outlet(const float* __restrict__ pop, float2* __restrict__ F,
-                                                    const float* __restrict__ hprev, float* __restrict__ hcur, KP k)
+__global__ __launch_bounds__(OBLOCK) void k19_outlet(const float* __restrict__ pop, float2* __restrict__ F,
+                                                     const float* __restrict__ hprev, float* __restrict__ hcur,
+                                                     float* __restrict__ dst, KP k)
 {
-    const Site s = site(k, k.nz - 1);
-    if (!s.valid) return;
+    Node nd;
+    nd.x = (int)(blockIdx.x * OBLOCK + threadIdx.x);
+    nd.y = (int)blockIdx.y;
+    nd.z = k.nz - 1;
+    if (nd.x >= k.nx) return;
+    nd.q = (uint32_t)nd.y * (uint32_t)k.nx + (uint32_t)nd.x;
     double d[Q19], fr[Q19];
-    node_state<GEN, LBM_BC_JET>(pop, hprev, k, s, d, fr);
+    if (GEN) {
+#pragma unroll
+        for (int i = 0; i < Q19; ++i) general_pop(pop, k, order_of(k, nd), i, d[i], fr[i]);
+    } else {
+        outlet_rule(pop, hprev, k, nd, d, fr);
+    }
     double rr = 0.0, rb = 0.0, m = 0.0;
     const size_t P = k.plane;
 #pragma unroll
@@ -337,128 +339,132 @@ __global__ __launch_bounds__(BLOCK) void k19_outlet(const float* __restrict__ po
         m += d[i];
         rr += fr[i];
         rb += d[i] + w19(i) * k.rho_b0 - fr[i];
-        hcur[(size_t)i * P + s.q] = (float)d[i];
-        hcur[(size_t)(Q19 + i) * P + s.q] = (float)fr[i];
+        hcur[(size_t)i * P + nd.q] = (float)d[i];
+        hcur[(size_t)(Q19 + i) * P + nd.q] = (float)fr[i];
     }
-    store_fields(F, k, s.n, rr, rb, m);
+    store_fields(F, k, order_of(k, nd), rr, rb, m);
+    if (inlet_inside(k, nd.x, nd.y)) {
+        const uint32_t row = row_of(k, nd.y, -1), rs = (uint32_t)k.rs;
+#pragma unroll
+        for (int i = 1; i < Q19; ++i)
+            if (kCZ[i] == 1)
+                dst[(size_t)row * (Q19 * rs) + (uint32_t)slot19(i) * rs + nd.x] =
+                    (float)(inlet_feq19(k, i, nd.x, nd.y, k.t) - w19(i) * k.rho_b0);
+        const_cast<float4*>(records(dst, k))[(size_t)row * rs + nd.x] = make_float4(-0.f, 0.f, 0.f, 0.f);
+    }
 }
 
-// (phi, rho - rho_b0) of the neighbour at offset (dx, dy, dz): periodic wrap,
-// or (jet) (1, rho_r0 - rho_b0) in the inlet circle at z = -1 and the clamped
-// node elsewhere outside (the mirrored field of the half-way walls and outlet)
-template <int BC, bool BOT = true>
-__device__ __forceinline__ float2 field_at(const float2* __restrict__ F, const KP& k, const Site& s, int dx, int dy,
-                                           int dz)
+// (phi, rho - rho_b0) at (x, y, z), which may lie one node outside: periodic wrap, or
+// (jet) (1, rho_r0 - rho_b0) in the inlet circle at z = -1 and the clamped
+// node elsewhere outside (the mirrored field of the half-way walls and outlet).
+// XIN: x lies inside.
+template <int BC, bool XIN = false>
+__device__ __forceinline__ float2 field_at(const float2* __restrict__ F, const KP& k, int x, int y, int z)
 {
-    if constexpr (BC == LBM_BC_PERIODIC) {
-        return F[at(s, dx, dy, dz)];
-    } else {
-        if (BOT && dz < 0 && s.z == 0 && inlet_inside(k, s.x + dx, s.y + dy))  // bottom plane only
-            return make_float2(1.f, k.rho_r0 - k.rho_b0);
-        // clamp per axis (selects)
-        const int ex = (s.x + dx < 0 || s.x + dx >= k.nx) ? 0 : dx;
-        const int ey = (s.y + dy < 0 || s.y + dy >= k.ny) ? 0 : dy;
-        const int ez = (s.z + dz < 0 || s.z + dz >= k.nz) ? 0 : dz;
-        return F[(uint32_t)((int)s.n + ex + ey * k.nx + ez * (int)k.plane)];
-    }
+    const bool in = BC == LBM_BC_JET && z < 0 && inlet_inside(k, x, y);
+    x = XIN ? x : BC == LBM_BC_PERIODIC ? wrapc(x, k.nx) : clampc(x, k.nx);
+    y = BC == LBM_BC_PERIODIC ? wrapc(y, k.ny) : clampc(y, k.ny);
+    z = BC == LBM_BC_PERIODIC ? wrapc(z, k.nz) : clampc(z, k.nz);
+    const float2 v = ldp(F, ((uint32_t)z * (uint32_t)k.ny + (uint32_t)y) * (uint32_t)k.nx + (uint32_t)x);
+    return in ? make_float2(1.f, k.rho_r0 - k.rho_b0) : v;
 }
 
 // isotropic gradients of phi and rho, 3 sum_i w_i chi(x + c_i) c_i, summed
 // over the opposite pairs (i, i + 1) as differences: exactly zero on a
 // uniform field, which keeps the recolouring off there
-template <int BC, bool BOT>
-__device__ __forceinline__ void gradients(const float2* __restrict__ F, const KP& k, const Site& s, double& gpx,
-                                          double& gpy, double& gpz, double& grx, double& gry, double& grz)
+template <int TX, int TY, int I = 1>
+__device__ __forceinline__ void gradients(const float2* __restrict__ win, const Tile& t, double& gpx, double& gpy,
+                                          double& gpz, double& grx, double& gry, double& grz)
 {
-#pragma unroll
-    for (int i = 1; i < Q19; i += 2) {
-        const float2 qp = field_at<BC, BOT>(F, k, s, kCX[i], kCY[i], kCZ[i]);
-        const float2 qm = field_at<BC, BOT>(F, k, s, -kCX[i], -kCY[i], -kCZ[i]);
-        const double tp = 3.0 * w19(i) * ((double)qp.x - (double)qm.x);
-        const double tr = 3.0 * w19(i) * ((double)qp.y - (double)qm.y);
-        if (kCX[i]) { gpx += kCX[i] * tp; grx += kCX[i] * tr; }
-        if (kCY[i]) { gpy += kCY[i] * tp; gry += kCY[i] * tr; }
-        if (kCZ[i]) { gpz += kCZ[i] * tp; grz += kCZ[i] * tr; }
+    if constexpr (I < Q19) {
+        const float2 qp = win[wslot<TX, TY>(t.lx, t.ly, kCX[I], kCY[I], kCZ[I])];
+        const float2 qm = win[wslot<TX, TY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
+        const double tp = 3.0 * w19(I) * ((double)qp.x - (double)qm.x);
+        const double tr = 3.0 * w19(I) * ((double)qp.y - (double)qm.y);
+        if (kCX[I]) { gpx += kCX[I] * tp; grx += kCX[I] * tr; }
+        if (kCY[I]) { gpy += kCY[I] * tp; gry += kCY[I] * tr; }
+        if (kCZ[I]) { gpz += kCZ[I] * tp; grz += kCZ[I] * tr; }
+        gradients<TX, TY, I + 2>(win, t, gpx, gpy, gpz, grx, gry, grz);
     }
+}
+
+// 1/sqrt(a) of a positive normal number: the hardware estimate and two Newton steps,
+// a few FP64 ulps
+__device__ __forceinline__ double inv_sqrt(double a)
+{
+    double r = __builtin_amdgcn_rsq(a);
+    r = fma(0.5 * r, fma(-a * r, r, 1.0), r);
+    return fma(0.5 * r, fma(-a * r, r, 1.0), r);
+}
+
+// the model's parameters as the kernels' FP64 arithmetic takes them (FP32 values:
+// converted once on the host instead of by every wavefront)
+struct Consts {
+    double rho_b0, alpha_b, dalpha, a_minus_w0, inv_nu_r, inv_nu_b, A, beta, eps2, g[3];
+};
+inline Consts consts_of(const KP& k)
+{
+    return Consts{k.rho_b0, k.alpha_b, k.dalpha, k.a_minus_w0, k.inv_nu_r, k.inv_nu_b, k.A, k.beta, k.eps2,
+                  {k.gx, k.gy, k.gz}};
 }
 
 // Collision, perturbation, recolouring and the store of the shifted form at the
 // node itself (the next step pulls from it), Sec. II: Eqs. Momentum to op3b.
-template <bool GEN, int BC>
+template <bool GEN, int BC, class TL, bool NT>
 __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ src, float* __restrict__ dst,
                                                      const float2* __restrict__ F, const float* __restrict__ hcur,
-                                                     KP k)
+                                                     KP k, Consts c)
 {
-    const Site s = site(k);
-    if (!s.valid) return;
+    constexpr int TX = TL::CX, TY = TL::CY;
+    __shared__ float2 win[TileShape<TX, TY>::W];
+    const Tile t = this_tile<TX, TY>(k);
+    const Node& nd = t.nd;
+    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return field_at<BC, true>(F, k, x, y, z); },
+                         [&](int x, int y, int z) { return field_at<BC>(F, k, x, y, z); },
+                         [&](int w, const float2& v) { win[w] = v; });
+    __syncthreads();
+    if (!nd.valid) return;
     const size_t N = k.N;
     float d[Q19];
-    if (BC == LBM_BC_JET && s.z == k.nz - 1) {  // the outlet plane: the density pass wrote it to hcur
+    if (BC == LBM_BC_JET && nd.z == k.nz - 1) {  // the outlet plane: its kernel wrote it to hcur
 #pragma unroll
-        for (int i = 0; i < Q19; ++i) d[i] = hcur[(size_t)i * k.plane + s.q];
+        for (int i = 0; i < Q19; ++i) d[i] = hcur[(size_t)i * k.plane + nd.q];
     } else if (GEN) {
 #pragma unroll
-        for (int i = 0; i < Q19; ++i) d[i] = src[(size_t)i * N + s.n];
-    } else if (BC == LBM_BC_JET && s.z == 0) {  // block-uniform
-#pragma unroll
-        for (int i = 0; i < Q19; ++i) {
-            double dd, fr;
-            pull_at<BC, true>(src, k, s, i, dd, fr);
-            d[i] = (float)dd;
-        }
+        for (int i = 0; i < Q19; ++i) d[i] = src[(size_t)i * N + order_of(k, nd)];
     } else {
-#pragma unroll
-        for (int i = 0; i < Q19; ++i) {
-            double dd, fr;
-            pull_at<BC, false>(src, k, s, i, dd, fr);
-            d[i] = (float)dd;
-        }
+        pull_all19<BC>(src, k, nd.y, nd.z, x_offsets<BC, float>(k, nd.x), d);
     }
-    const float2 P = F[s.n], Q = F[(size_t)k.N + s.n];
+    const float2 P = win[wslot<TX, TY>(t.lx, t.ly, 0, 0, 0)], Q = ldp(F + k.N, order_of(k, nd));
     const double phi = P.x, m = P.y, rr = Q.x, rb = Q.y;
     double gpx = 0, gpy = 0, gpz = 0, grx = 0, gry = 0, grz = 0;
-    if (BC == LBM_BC_JET && s.z == 0)  // block-uniform
-        gradients<BC, true>(F, k, s, gpx, gpy, gpz, grx, gry, grz);
-    else
-        gradients<BC, false>(F, k, s, gpx, gpy, gpz, grx, gry, grz);
+    gradients<TX, TY>(win, t, gpx, gpy, gpz, grx, gry, grz);
     // interpolated properties, body force, velocity (Eqs. bodyForceJet, Momentum)
-    const double rho = k.rho_b0 + m;
+    const double rho = c.rho_b0 + m;
     const double hp = 0.5 * (1.0 + phi);
-    const double ab = (double)k.alpha_b + hp * (double)k.dalpha;
-    const double amw = (double)k.a_minus_w0 + hp * (double)k.dalpha;  // alpha_bar - 1/3
-    const double nub = 1.0 / (hp * (double)k.inv_nu_r + (1.0 - hp) * (double)k.inv_nu_b);
-    const double s2 = 1.0 / (3.0 * nub + 0.5);
-    const double Fx = m * k.gx, Fy = m * k.gy, Fz = m * k.gz;
-    double jx = 0, jy = 0, jz = 0;
+    const double ab = c.alpha_b + hp * c.dalpha;
+    const double amw = c.a_minus_w0 + hp * c.dalpha;  // alpha_bar - 1/3
+    const double nub = div_fields(1.0, hp * c.inv_nu_r + (1.0 - hp) * c.inv_nu_b);
+    const double s2 = div_fields(1.0, 3.0 * nub + 0.5);
+    const double Fx = m * c.g[0], Fy = m * c.g[1], Fz = m * c.g[2];
+    // momentum and second moments of d over opposite pairs (i, i + 1)
+    double jx = 0, jy = 0, jz = 0, pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
 #pragma unroll
-    for (int i = 1; i < Q19; ++i) {
-        if (kCX[i]) jx += kCX[i] * (double)d[i];
-        if (kCY[i]) jy += kCY[i] * (double)d[i];
-        if (kCZ[i]) jz += kCZ[i] * (double)d[i];
+    for (int i = 1; i < Q19; i += 2) {
+        const double sp = (double)d[i] + (double)d[i + 1], df = (double)d[i] - (double)d[i + 1];
+        if (kCX[i]) { jx += kCX[i] * df; pxx += sp; }
+        if (kCY[i]) { jy += kCY[i] * df; pyy += sp; }
+        if (kCZ[i]) { jz += kCZ[i] * df; pzz += sp; }
+        if (kCX[i] * kCY[i]) pxy += (kCX[i] * kCY[i]) * sp;
+        if (kCX[i] * kCZ[i]) pxz += (kCX[i] * kCZ[i]) * sp;
+        if (kCY[i] * kCZ[i]) pyz += (kCY[i] * kCZ[i]) * sp;
     }
-    const double irho = 1.0 / rho;
+    const double irho = div_fields(1.0, rho);
     const double ux = (jx + 0.5 * Fx) * irho, uy = (jy + 0.5 * Fy) * irho, uz = (jz + 0.5 * Fz) * irho;
     const double u2 = ux * ux + uy * uy + uz * uz;
     const double udr = ux * grx + uy * gry + uz * grz;
     const double uF = ux * Fx + uy * Fy + uz * Fz;
-    const double kap = 1.5 * (1.0 - ab) * m - 1.5 * amw * k.rho_b0;  // 1.5 (1 - ab) rho - rho_b0
-    // e_i = feq_i - w_i rho_b0 (Eq. EES, Eq. Phi) plus half the forcing
-    // population (Eq. ketFd): the post-collision value without the
-    // non-equilibrium part
-    auto eq_half_force = [&](int i) -> double {
-        const double cu = kCX[i] * ux + kCY[i] * uy + kCZ[i] * uz;
-        const double cF = kCX[i] * Fx + kCY[i] * Fy + kCZ[i] * Fz;
-        const double poly = cu * (3.0 + 4.5 * cu - 4.5 * u2 + 4.5 * cu * cu) - 1.5 * u2;
-        double e;
-        if (i == 0) {
-            e = rho * amw + m * (1.0 / 3.0) + rho * w19(0) * poly - 3.0 * nub * udr;
-        } else {
-            const double cg = kCX[i] * grx + kCY[i] * gry + kCZ[i] * grz;
-            const double mi = csq(i) == 1 ? 0.5 : 0.25;  // m_i / 4
-            e = w19(i) * (kap + rho * poly) + mi * nub * cu * cg;
-        }
-        return e + 0.5 * w19(i) * (3.0 * (cF - uF) + 9.0 * cu * cF);
-    };
+    const double kap = 1.5 * (1.0 - ab) * m - 1.5 * amw * c.rho_b0;  // 1.5 (1 - ab) rho - rho_b0
     // Pi^g of g = f - feq + F'/2 from closed forms of the moments of feq and F'
     // (both lattices' coefficients give them): sum feq c c = rho [(1 - ab)/2 I
     // + u u] + nu_bar [u grad rho + grad rho u + (u . grad rho) I] (Eqs. EES,
@@ -466,17 +472,6 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
     // Only the deviatoric part is used, so the isotropic terms are left out:
     // dev Pi^g = dev [sum d c c - rho u u - nu_bar (u grad rho + grad rho u)
     //                 + (u F + F u)/2]
-    double pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
-#pragma unroll
-    for (int i = 1; i < Q19; ++i) {
-        const double g = (double)d[i];
-        if (kCX[i]) pxx += g;
-        if (kCY[i]) pyy += g;
-        if (kCZ[i]) pzz += g;
-        if (kCX[i] && kCY[i]) pxy += kCX[i] * kCY[i] * g;
-        if (kCX[i] && kCZ[i]) pxz += kCX[i] * kCZ[i] * g;
-        if (kCY[i] && kCZ[i]) pyz += kCY[i] * kCZ[i] * g;
-    }
     pxx += -rho * ux * ux - 2.0 * nub * ux * grx + ux * Fx;
     pyy += -rho * uy * uy - 2.0 * nub * uy * gry + uy * Fy;
     pzz += -rho * uz * uz - 2.0 * nub * uz * grz + uz * Fz;
@@ -496,42 +491,75 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
     const double m022 = uz * uz * k020 + uy * uy * k002 + 4.0 * uy * uz * k011;
     // perturbation (Eq. perturb, Eq. B_i) and recolouring record (Eqs. op3r/op3b)
     const double G2 = gpx * gpx + gpy * gpy + gpz * gpz;
-    const bool on = G2 > (double)k.eps2;
-    const double gn = on ? sqrt(G2) : 0.0;
-    const double Ag = on ? k.A * gn : 0.0;  // A |grad phi|
-    const double iG2 = on ? 1.0 / G2 : 0.0;
-    const double rc = rr + rb;
-    const double vs = on ? k.beta * rr * rb / rc * (1.0 - ab) / gn : 0.0;
+    const bool on = G2 > c.eps2;
+    const double ign = on ? inv_sqrt(G2) : 0.0;
+    const double Agn = c.A * G2 * ign, Aign = c.A * ign;  // A |grad phi|, A / |grad phi|
+    const double irc = div_fields(1.0, rr + rb);
+    const double vs = c.beta * rr * rb * irc * (1.0 - ab) * ign;
+    // jet, bottom plane: the ghost cell below mirrors this node outside the inlet
+    const uint32_t row = row_of(k, nd.y, nd.z), rsB = 4u * (uint32_t)k.rs, xB = 4u * (uint32_t)nd.x;
+    const bool bottom = BC == LBM_BC_JET && nd.z == 0;
+    const bool gcell = bottom && !inlet_inside(k, nd.x, nd.y);
+    const uint32_t grow = BC == LBM_BC_JET ? row_of(k, nd.y, -1) : 0u;
+    const auto rd = row_rsrc(dst + (size_t)row * (uint32_t)(Q19 * k.rs), (uint32_t)(Q19 * k.rs));
+    const auto rg = row_rsrc(dst + (size_t)grow * (uint32_t)(Q19 * k.rs), (uint32_t)(Q19 * k.rs));
+    const auto store = [&](int i, double f) {
+        const float v = (float)f;
+        st_row<NT>(rd, xB, (uint32_t)slot19(i) * rsB, v);
+        if (BC == LBM_BC_JET && kCZ[i] < 0 && bottom) {  // uniform: leaves downwards
+            if (gcell) st_row<NT>(rg, xB, (uint32_t)slot19(mirror_dir(i, 4)) * rsB, v);
+        }
+    };
+    // rest population
+    store(0, rho * amw + m * (1.0 / 3.0) - 0.5 * rho * u2 - 3.0 * nub * udr - 0.5 * uF + Agn * (1.0 / 3.0) +
+                 (m220 + m202 + m022) - (k200 + k020 + k002));
+    // Opposite pairs: with m_i / 4 = 9 w_i the terms of feq, F'/2 and the perturbation
+    // share one factor w_i,
+    //   even = kappa' - 1.5 rho u^2 - 1.5 u.F - A |g| + cu (4.5 rho cu + 9 nu cr + 4.5 cF) + A/|g| cg^2,
+    //   odd  = cu (rho (3 - 4.5 u^2) + 4.5 rho cu^2) + 1.5 cF
+    // (cu = c.u, cr = c.grad rho, cF = c.F, cg = c.grad phi); h, the part of the
+    // relaxed moments, splits the same way.
+    const double K0 = kap - 1.5 * rho * u2 - 1.5 * uF - Agn, K1 = rho * (3.0 - 4.5 * u2), r45 = 4.5 * rho;
+    const double nub9 = 9.0 * nub;
+    // 9 nu grad rho + 4.5 F and 1.5 F
+    const double qx = nub9 * grx + 4.5 * Fx, qy = nub9 * gry + 4.5 * Fy, qz = nub9 * grz + 4.5 * Fz;
+    const double sx = 1.5 * Fx, sy = 1.5 * Fy, sz = 1.5 * Fz;
 #pragma unroll
-    for (int i = 0; i < Q19; ++i) {
+    for (int i = 1; i < Q19; i += 2) {
         const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
-        double h;
-        if (cx && cy)
-            h = 0.25 * (m220 + cx * m120 + cy * m210 + cx * cy * k110);
-        else if (cx && cz)
-            h = 0.25 * (m202 + cx * m102 + cz * m201 + cx * cz * k101);
-        else if (cy && cz)
-            h = 0.25 * (m022 + cy * m012 + cz * m021 + cy * cz * k011);
-        else if (cx)
-            h = 0.5 * ((k200 - m220 - m202) - cx * (m120 + m102));
-        else if (cy)
-            h = 0.5 * ((k020 - m220 - m022) - cy * (m210 + m012));
-        else if (cz)
-            h = 0.5 * ((k002 - m202 - m022) - cz * (m201 + m021));
-        else
-            h = (m220 + m202 + m022) - (k200 + k020 + k002);
-        const double cgp = cx * gpx + cy * gpy + cz * gpz;
-        const double Bi = i == 0 ? -1.0 / 3.0 : w19(i);
-        const double pert = Ag * (w19(i) * cgp * cgp * iG2 - Bi);
-        dst[(size_t)i * N + s.n] = (float)(eq_half_force(i) + h + pert);
+        double he, ho;
+        if (cx && cy) {
+            he = 0.25 * (m220 + (cx * cy) * k110);
+            ho = 0.25 * (cx * m120 + cy * m210);
+        } else if (cx && cz) {
+            he = 0.25 * (m202 + (cx * cz) * k101);
+            ho = 0.25 * (cx * m102 + cz * m201);
+        } else if (cy && cz) {
+            he = 0.25 * (m022 + (cy * cz) * k011);
+            ho = 0.25 * (cy * m012 + cz * m021);
+        } else if (cx) {
+            he = 0.5 * (k200 - m220 - m202);
+            ho = -0.5 * cx * (m120 + m102);
+        } else if (cy) {
+            he = 0.5 * (k020 - m220 - m022);
+            ho = -0.5 * cy * (m210 + m012);
+        } else {
+            he = 0.5 * (k002 - m202 - m022);
+            ho = -0.5 * cz * (m201 + m021);
+        }
+        const double cu = cdot(i, ux, uy, uz), cg = cdot(i, gpx, gpy, gpz);
+        const double v = r45 * cu;
+        const double even = he + w19(i) * (K0 + cu * (v + cdot(i, qx, qy, qz)) + (Aign * cg) * cg);
+        const double odd = ho + w19(i) * (cu * (K1 + v * cu) + cdot(i, sx, sy, sz));
+        store(i, even + odd);
+        store(i + 1, even - odd);
     }
     // minority fraction: rho_r / rho, or -rho_b / rho (sign bit set, also for 0)
-    const float xm = rr <= rb ? (float)(rr / rc) : -(float)(rb / rc);
-    float* R = (float*)((char*)dst + rec_offset(N));
-    R[s.n] = xm;
-    R[N + s.n] = (float)(vs * gpx);
-    R[2 * N + s.n] = (float)(vs * gpy);
-    R[3 * N + s.n] = (float)(vs * gpz);
+    const float xm = rr <= rb ? (float)(rr * irc) : -(float)(rb * irc);
+    const float4 rv = make_float4(xm, (float)(vs * gpx), (float)(vs * gpy), (float)(vs * gpz));
+    float4* R = const_cast<float4*>(records(dst, k));
+    st_rec<NT>(R, k, row, nd.x, rv);
+    if (gcell) st_rec<NT>(R, k, grow, nd.x, mirror_rec(rv, 4));
 }
 
 // Macroscopic fields (node order) and FP64 audit partial sums, one slot per block.
@@ -541,11 +569,16 @@ __global__ __launch_bounds__(BLOCK) void k19_macro(const float* __restrict__ pop
                                                    float* __restrict__ o_u, float* __restrict__ o_phi,
                                                    double* __restrict__ partials)
 {
-    const Site s = site(k);
+    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
+    const Tile t = this_tile<STX, STY>(k);
+    if (!GEN) {
+        stage_records19<BC, STX, STY>(pop, k, t, win);
+        __syncthreads();
+    }
     double acc[5] = {0, 0, 0, 0, 0};
-    if (s.valid) {
+    if (t.nd.valid) {
         double d[Q19], fv[Q19];
-        node_state<GEN, BC>(pop, hist, k, s, d, fv);
+        node_state<GEN, BC>(pop, hist, k, t, win, d, fv);
         double m0 = 0.0, rr = 0.0, rb = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
 #pragma unroll
         for (int i = 0; i < Q19; ++i) {
@@ -558,7 +591,7 @@ __global__ __launch_bounds__(BLOCK) void k19_macro(const float* __restrict__ pop
         }
         const double rho = (double)k.rho_b0 + m0;
         const double px = jx + 0.5 * m0 * k.gx, py = jy + 0.5 * m0 * k.gy, pz = jz + 0.5 * m0 * k.gz;
-        const size_t n = s.n;
+        const size_t n = order_of(k, t.nd);
         if (o_rr) o_rr[n] = (float)rr;
         if (o_rb) o_rb[n] = (float)rb;
         if (o_u) {
@@ -584,15 +617,20 @@ template <bool GEN, int BC>
 __global__ __launch_bounds__(BLOCK) void k19_get_state(const float* __restrict__ pop, const float* __restrict__ hist,
                                                        KP k, float* __restrict__ st)
 {
-    const Site s = site(k);
-    if (!s.valid) return;
-    const size_t N = k.N;
+    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
+    const Tile t = this_tile<STX, STY>(k);
+    if (!GEN) {
+        stage_records19<BC, STX, STY>(pop, k, t, win);
+        __syncthreads();
+    }
+    if (!t.nd.valid) return;
+    const size_t N = k.N, n = order_of(k, t.nd);
     double d[Q19], fr[Q19];
-    node_state<GEN, BC>(pop, hist, k, s, d, fr);
+    node_state<GEN, BC>(pop, hist, k, t, win, d, fr);
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
-        st[(size_t)i * N + s.n] = (float)fr[i];
-        st[(size_t)(Q19 + i) * N + s.n] = (float)(d[i] + w19(i) * k.rho_b0 - fr[i]);
+        st[(size_t)i * N + n] = (float)fr[i];
+        st[(size_t)(Q19 + i) * N + n] = (float)(d[i] + w19(i) * k.rho_b0 - fr[i]);
     }
 }
 
@@ -603,11 +641,16 @@ template <bool GEN, int BC>
 __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__ pop, const float* __restrict__ hist,
                                                        KP k, DiagWork w)
 {
-    const Site s = site(k);
+    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
+    const Tile t = this_tile<STX, STY>(k);
+    if (!GEN) {
+        stage_records19<BC, STX, STY>(pop, k, t, win);
+        __syncthreads();
+    }
     bool fg = false;
-    if (s.valid) {
+    if (t.nd.valid) {
         double d[Q19], fr[Q19];
-        node_state<GEN, BC>(pop, hist, k, s, d, fr);
+        node_state<GEN, BC>(pop, hist, k, t, win, d, fr);
         double rr = 0.0, rb = 0.0;
 #pragma unroll
         for (int i = 0; i < Q19; ++i) {
@@ -618,9 +661,9 @@ __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__
         fg = (float)((a - b) / (a + b)) > 0.f;
     }
     const unsigned long long m = __ballot(fg);
-    const int run = diag_run_label(m, s.x == 0, (int)s.n);
-    if (s.valid) w.label[s.n] = fg ? run : -1;
-    diag_tally(w, m, fg ? s.z : -1);
+    const int i = (int)order_of(k, t.nd), run = diag_run_label(m, i);
+    if (t.nd.valid) w.label[i] = fg ? run : -1;
+    diag_tally(w, m, fg ? t.nd.z : -1);
 }
 
 // general form of one node from FP64 colour populations: the deviations rounded
@@ -647,16 +690,16 @@ __device__ __forceinline__ void put_general(float* __restrict__ dst, const KP& k
 // a caller state (lbm_get_state layout) into the general form
 __global__ __launch_bounds__(BLOCK) void k19_set_state(float* __restrict__ dst, KP k, const float* __restrict__ st)
 {
-    const Site s = site(k);
-    if (!s.valid) return;
-    const size_t N = k.N;
+    const Node nd = this_node(k);
+    if (!nd.valid) return;
+    const size_t N = k.N, n = order_of(k, nd);
     double fr[Q19], fb[Q19];
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
-        fr[i] = st[(size_t)i * N + s.n];
-        fb[i] = st[(size_t)(Q19 + i) * N + s.n];
+        fr[i] = st[(size_t)i * N + n];
+        fb[i] = st[(size_t)(Q19 + i) * N + n];
     }
-    put_general(dst, k, s.n, fr, fb);
+    put_general(dst, k, (uint32_t)n, fr, fb);
 }
 
 // Initial state (general form): per-colour equilibria rho_k {varphi_i(alpha_k) +
@@ -668,13 +711,12 @@ __global__ __launch_bounds__(BLOCK) void k19_init(float* __restrict__ dst, KP k,
                                                   double R, double W, double rho_r0, double rho_b0, double alpha_r,
                                                   double alpha_b)
 {
-    const Site s = site(k);
-    if (!s.valid) return;
-    const uint32_t z = s.zs[1] / k.plane, p = s.n - s.zs[1];
-    const uint32_t y = p / (uint32_t)k.nx, x = p - y * (uint32_t)k.nx;
+    const Node nd = this_node(k);
+    if (!nd.valid) return;
+    const uint32_t n = order_of(k, nd);
     double rr, rb, ux = 0, uy = 0, uz = 0;
     if (kind == LBM_INIT_DROPLET) {
-        const double dx = x - dcx, dy = y - dcy, dz = z - dcz;
+        const double dx = nd.x - dcx, dy = nd.y - dcy, dz = nd.z - dcz;
         const double th = tanh(2.0 * (sqrt(dx * dx + dy * dy + dz * dz) - R) / W);
         rr = 0.5 * rho_r0 * (1.0 - th);
         rb = 0.5 * rho_b0 * (1.0 + th);
@@ -682,12 +724,12 @@ __global__ __launch_bounds__(BLOCK) void k19_init(float* __restrict__ dst, KP k,
         rr = 0.0;
         rb = rho_b0;
     } else {
-        rr = frr[s.n];
-        rb = frb[s.n];
+        rr = frr[n];
+        rb = frb[n];
         if (fu) {
-            ux = fu[3 * (size_t)s.n];
-            uy = fu[3 * (size_t)s.n + 1];
-            uz = fu[3 * (size_t)s.n + 2];
+            ux = fu[3 * (size_t)n];
+            uy = fu[3 * (size_t)n + 1];
+            uz = fu[3 * (size_t)n + 2];
         }
     }
     const double u2 = ux * ux + uy * uy + uz * uz;
@@ -701,7 +743,7 @@ __global__ __launch_bounds__(BLOCK) void k19_init(float* __restrict__ dst, KP k,
         fr[i] = rr * (phr + wp);
         fb[i] = rb * (phb + wp);
     }
-    put_general(dst, k, s.n, fr, fb);
+    put_general(dst, k, n, fr, fb);
 }
 
 }  // namespace q19

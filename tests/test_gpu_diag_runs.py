@@ -1,7 +1,6 @@
 """The union-find of the jet diagnostics where its runs along x begin and end: row
-lengths around the 64-node segments, on both lattices (D3Q19 cuts segments out of
-the plane index, D3Q27 out of x), and lattices with fewer planes than a counting
-thread takes and with a remainder.  Site-percolation fields (every node drawn by
+lengths around the 64-node segments, on both lattices, and lattices with fewer
+planes than a counting thread takes and with a remainder.  Site-percolation fields (every node drawn by
 itself) make runs of every length and components that join through all three
 axes.  Whole numbers, compared exactly with the CPU reference on the GPU's own phi.
 """
