@@ -58,9 +58,10 @@ struct lbm_handle {
     dim3 grid_dtiles;   // stencil tiles of the density pass
     dim3 grid_rows;     // one plane by row segments (outlet)
     dim3 grid_plane;    // one plane
+    dim3 grid_adj;      // adjoint: every interior plane
     dim3 grid_shell;    // ghost shell cells (adjoint)
     uint32_t ncells;    // ghost shell cell count
-    int nblk;           // blocks of grid_all (adjoint partial slots)
+    int nblk;           // blocks of the adjoint's node kernel (its partial slots)
     int tiles;          // tiles of the step kernels (step_tiles)
     int nt;             // the state is larger than the memory-side cache
     int naud;           // blocks of the macroscopic kernel (audit partial slots)
@@ -319,6 +320,13 @@ int with_tiles(int tiles, F&& f)
     }
 }
 
+// tiles of the adjoint kernels, whatever the storage of the state
+dim3 adjoint_grid(const lbm_params* p)
+{
+    return step_tiles(p) == TILES_WIDE ? tile_grid<WideTiles::CX, WideTiles::CY>(p->nx, p->ny, p->nz)
+                                       : tile_grid<NarrowTiles::CX, NarrowTiles::CY>(p->nx, p->ny, p->nz);
+}
+
 bool aligned(const void* ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
 // parameters for reading the current state
@@ -394,7 +402,6 @@ int lbm_query_sizes(const lbm_params* p, lbm_sizes* out)
     const uint64_t N = (uint64_t)p->nx * p->ny * p->nz;
     const uint64_t NP = padded_nodes(p);
     const uint64_t plane = (uint64_t)p->nx * p->ny;
-    const uint64_t nblk = ((plane + BLOCK - 1) / BLOCK) * (uint64_t)p->nz;
     out->n_nodes = N;
     if (is_q19(p)) {
         out->pop_bytes = q19::pop_bytes(N);
@@ -412,7 +419,7 @@ int lbm_query_sizes(const lbm_params* p, lbm_sizes* out)
     out->hist_bytes = p->bc == LBM_BC_JET ? 2ull * 2ull * Q * plane * sizeof(float) : 0;
     out->audit_bytes = (audit_blocks(p) + 1) * 5 * sizeof(double);
     out->inlet_bytes = plane * sizeof(float);
-    out->adjoint_bytes = adjoint_layout(NP, N, plane, nblk, nullptr, nullptr);
+    out->adjoint_bytes = adjoint_layout(NP, N, plane, blocks_of(adjoint_grid(p)), nullptr, nullptr);
     out->state_bytes = 2ull * Q * N * sizeof(float);
     out->snap_bytes = snap_layout(p, nullptr, nullptr);
     return LBM_OK;
@@ -483,7 +490,8 @@ int lbm_init(lbm_handle** h, const lbm_params* p, const lbm_buffers* buf, const 
     const uint64_t cells = 2ull * H->k.px * H->k.py + 2ull * H->k.px * p->nz + 2ull * p->ny * p->nz;
     H->ncells = (uint32_t)cells;
     H->grid_shell = dim3((unsigned)((cells + BLOCK - 1) / BLOCK));
-    H->nblk = (int)(H->grid_all.x * H->grid_all.y);
+    H->grid_adj = adjoint_grid(p);
+    H->nblk = (int)blocks_of(H->grid_adj);
     H->naud = (int)audit_blocks(p);
     const SnapBytes sb = snap_bytes_of(p);
     H->nt = (H->q19 ? 92ull * H->k.n19 : (uint64_t)sb.pop + sb.rec) > kCacheBytes;
@@ -854,14 +862,21 @@ int adjoint_rest(lbm_handle* h, const KP& k, const AdjWork& w, const float* htop
                            w.ML, w.DL, k);
         LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(k_adj_node<BC>, h->grid_all, dim3(BLOCK), 0, h->stream, w.MOM, lambda_in, w.ML, h->PD, h->XR,
-                       w.LC, w.AG0, w.AG1, w.AP, k);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_adj_ghosts<BC>, h->grid_shell, dim3(BLOCK), 0, h->stream, w.AG0, w.AG1, w.GH, k, h->ncells);
-    LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_adj_fields<BC>, h->grid_tiles, dim3(BLOCK), 0, h->stream, w.AG0, w.AG1, w.GH, h->PD, h->XR,
-                       w.DL, w.LC, lambda_out, k);
-    LAUNCH_CHECK();
+    const int rc = with_tiles<StF32>(h->tiles, [&](auto tl) -> int {
+        using TL = decltype(tl);
+        hipLaunchKernelGGL((k_adj_node<BC, TL>), h->grid_adj, dim3(BLOCK), 0, h->stream, w.MOM, lambda_in, w.ML, h->PD,
+                           h->XR, w.LC, w.AG0, w.AG1, w.AP, k);
+        LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_adj_ghosts<BC>, h->grid_shell, dim3(BLOCK), 0, h->stream, w.AG0, w.AG1, w.GH, k,
+                           h->ncells);
+        LAUNCH_CHECK();
+        const bool nt = 2ull * Q * h->k.N * sizeof(float) > kCacheBytes;
+        hipLaunchKernelGGL((nt ? k_adj_fields<BC, TL, true> : k_adj_fields<BC, TL, false>), h->grid_adj, dim3(BLOCK),
+                           0, h->stream, w.AG0, w.AG1, w.GH, h->PD, h->XR, w.DL, w.LC, lambda_out, k);
+        LAUNCH_CHECK();
+        return LBM_OK;
+    });
+    if (rc != LBM_OK) return rc;
     if (BC == LBM_BC_JET && dJ_du_in) {
         hipLaunchKernelGGL(k_adj_inlet, h->grid_plane, dim3(BLOCK), 0, h->stream, lambda_in, dJ_du_in, k);
         LAUNCH_CHECK();

@@ -82,6 +82,29 @@ __device__ __forceinline__ uint32_t nidx(const KP& k, int x, int y, int z)
     return ((uint32_t)z * (uint32_t)k.ny + (uint32_t)y) * (uint32_t)k.nx + (uint32_t)x;
 }
 
+// node x of a row of nx values at a uniform address
+__device__ __forceinline__ float ld_lane(const float* base, int nx, int x)
+{
+    return ld_row<float>(row_rsrc(base, (uint32_t)nx), (uint32_t)x * 4u, 0u);
+}
+template <bool NT>
+__device__ __forceinline__ void st_lane(float* base, int nx, int x, float v)
+{
+    st_row<NT>(row_rsrc(base, (uint32_t)nx), (uint32_t)x * 4u, 0u, v);
+}
+// first three components of the stencil cotangents of node x, row (y, z) uniform
+__device__ __forceinline__ float3 ld_cot(const float4* __restrict__ AG, const KP& k, int x, int y, int z)
+{
+    const auto r = row_rsrc(AG + pidx(k, -1, y, z), (uint32_t)k.px);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, (uint32_t)(x + 1) * 16u, 0, 0);
+    return make_float3(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]));
+}
+__device__ __forceinline__ float3 cot_at(const float4* __restrict__ AG, const KP& k, int x, int y, int z)
+{
+    const float4 v = ldp(AG, pidx(k, x, y, z));
+    return make_float3(v.x, v.y, v.z);
+}
+
 // 1. densities and raw moments of the deviations d_i = f^r_i + f^b_i - w_i rho_b0
 // of an FP32 state (fr planes, then fb), accumulated in FP64
 __global__ __launch_bounds__(BLOCK) void k_adj_density(const float* __restrict__ st, float2* __restrict__ PD,
@@ -213,91 +236,172 @@ __global__ __launch_bounds__(BLOCK) void k_adj_outlet(const float* __restrict__ 
 }
 
 // 3. reverse streaming and node VJP
-// direction I with the components in mask m reversed, by selects (m varies per lane)
-template <int I>
-__device__ __forceinline__ int mirror_sel(int m)
+// Where the cotangents of a node's post-collision populations lie.  The lattice rows
+// y + c_y and z + c_z, the reflections on y and z and the planes that the outlet
+// condition replaces are uniform over the wavefront (it lies in one row); along x
+// a lane at the wall reads itself in the direction reversed on x.
+struct GatherRows {
+    const float* base[3];  // [c_z + 1] plane z + c_z of population 0
+    size_t stride[3];      // from population to population
+    bool lost[3];          // overwritten by the outlet condition
+    uint32_t row[3];       // [c_y + 1] first node of row y + c_y in its plane
+    bool my[2];            // [c_y > 0] reflected on y
+    bool mz;               // reflected on z (c_z = -1)
+};
+template <int BC>
+__device__ __forceinline__ GatherRows gather_rows(const KP& k, const float* __restrict__ lam,
+                                                  const float* __restrict__ ML, int y, int z)
 {
-    constexpr int t0 = mirror_dir(I, 0), t1 = mirror_dir(I, 1), t2 = mirror_dir(I, 2), t3 = mirror_dir(I, 3);
-    constexpr int t4 = mirror_dir(I, 4), t5 = mirror_dir(I, 5), t6 = mirror_dir(I, 6), t7 = mirror_dir(I, 7);
-    return (m & 4) ? ((m & 2) ? ((m & 1) ? t7 : t6) : ((m & 1) ? t5 : t4))
-                   : ((m & 2) ? ((m & 1) ? t3 : t2) : ((m & 1) ? t1 : t0));
+    GatherRows g;
+    g.mz = BC == LBM_BC_JET && z == 0;
+#pragma unroll
+    for (int c = -1; c <= 1; ++c) {
+        int zs = z + c, ys = y + c;
+        g.lost[c + 1] = false;
+        if (BC == LBM_BC_PERIODIC) {
+            zs = wrapc(zs, k.nz);
+            ys = wrapc(ys, k.ny);
+        } else {
+            if (c < 0 && g.mz) zs = 0;
+            g.lost[c + 1] = c >= 0 && zs >= k.nz - 1;
+            if (g.lost[c + 1]) zs = k.nz - 2;  // any plane: the value is dropped
+            if (c != 0) g.my[c > 0] = ys < 0 || ys >= k.ny;
+            ys = clampc(ys, k.ny);
+        }
+        const bool below = BC == LBM_BC_JET && zs == k.nz - 2;  // the plane under the outlet
+        g.base[c + 1] = below ? ML : lam + (size_t)zs * k.plane;
+        g.stride[c + 1] = below ? (size_t)k.plane : (size_t)k.N;
+        g.row[c + 1] = (uint32_t)ys * (uint32_t)k.nx;
+    }
+    return g;
 }
 
-// cotangents of the post-collision populations of this node: those of the
-// populations they become after streaming (x + c_i, reversed on every axis
-// that leaves the lattice), zero where the forward step overwrites them
+// lane offsets along x of c_x = +1 and -1, and (jet) the lanes at the walls
+struct XSide {
+    int p, m;
+    bool wp, wm;
+    bool inlet;  // the node below the lane is an inlet cell: overwritten by the inflow
+};
+
+// cotangents of the post-collision population I of this node, red and blue: those of
+// the population it becomes after streaming (x + c_i, reversed on every axis
+// that leaves the lattice), zero where the forward step overwrites it
+template <int BC, int I>
+__device__ __forceinline__ void adj_gather_dir(const GatherRows& g, int x, const XSide& xs, float& vr, float& vb)
+{
+    constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
+    const float* p = g.base[cz + 1] + g.row[cy + 1];
+    const size_t stride = g.stride[cz + 1];
+    const int xo = cx > 0 ? xs.p : (cx < 0 ? xs.m : x);
+    if constexpr (BC == LBM_BC_PERIODIC) {
+        p += I * stride;
+        vr = ldp(p, (uint32_t)xo);
+        vb = ldp(p + Q * stride, (uint32_t)xo);
+    } else {
+        const bool my = cy != 0 && g.my[cy > 0], mz = cz < 0 && g.mz;
+        const int j = my ? (mz ? dir_of(cx, -cy, -cz) : dir_of(cx, -cy, cz)) : (mz ? dir_of(cx, cy, -cz) : I);
+        p += (size_t)j * stride;
+        const float* pb = p + Q * stride;
+        if constexpr (cx == 0) {
+            vr = ldp(p, (uint32_t)x);
+            vb = ldp(pb, (uint32_t)x);
+        } else {
+            const int jm = my ? (mz ? dir_of(-cx, -cy, -cz) : dir_of(-cx, -cy, cz))
+                              : (mz ? dir_of(-cx, cy, -cz) : dir_of(-cx, cy, cz));
+            const bool wall = cx > 0 ? xs.wp : xs.wm;
+            const int64_t o = wall ? (int64_t)(jm - j) * (int64_t)stride + x : (int64_t)xo;
+            vr = p[o];
+            vb = pb[o];
+        }
+    }
+}
 template <int BC, int I = 0>
-__device__ __forceinline__ void adj_gather(const KP& k, const float* __restrict__ lam, const float* __restrict__ ML,
-                                           const Node& nd, float* Lr, float* Lb)
+__device__ __forceinline__ void adj_gather(const GatherRows& g, int x, const XSide& xs, float* Lr, float* Lb)
 {
     if constexpr (I < Q) {
-        const size_t N = k.N;
-        constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
-        int dx = nd.x + cx, dy = nd.y + cy, dz = nd.z + cz;
-        float vr = 0.f, vb = 0.f;
-        if (BC == LBM_BC_PERIODIC) {
-            if (cx) dx = wrapc(dx, k.nx);
-            if (cy) dy = wrapc(dy, k.ny);
-            if (cz) dz = wrapc(dz, k.nz);
-            const size_t n = nidx(k, dx, dy, dz);
-            vr = lam[(size_t)I * N + n];
-            vb = lam[(size_t)(Q + I) * N + n];
-        } else {
-            int m = 0;
-            bool lost = false;
-            if (cx && (dx < 0 || dx >= k.nx)) { m |= 1; dx = nd.x; }
-            if (cy && (dy < 0 || dy >= k.ny)) { m |= 2; dy = nd.y; }
-            if (cz < 0 && dz < 0) {
-                // the ghost below this node is an inlet cell: overwritten by the inflow
-                if (m == 0 && inlet_inside(k, nd.x, nd.y)) lost = true;
-                m |= 4;
-                dz = nd.z;
-            }
-            if (cz > 0 && dz >= k.nz - 1) lost = true;   // replaced by the convective condition
-            if (cz == 0 && dz == k.nz - 1) lost = true;
-            if (!lost) {
-                const int j = cx || cy || cz < 0 ? mirror_sel<I>(m) : I;
-                if (dz == k.nz - 2) {
-                    const size_t q = (size_t)dy * k.nx + dx;
-                    vr = ML[(size_t)j * k.plane + q];
-                    vb = ML[(size_t)(Q + j) * k.plane + q];
-                } else {
-                    const size_t n = nidx(k, dx, dy, dz);
-                    vr = lam[(size_t)j * N + n];
-                    vb = lam[(size_t)(Q + j) * N + n];
-                }
-            }
+        adj_gather_dir<BC, I>(g, x, xs, Lr[I], Lb[I]);
+        adj_gather<BC, I + 1>(g, x, xs, Lr, Lb);
+    }
+}
+// zero for the populations that the forward step overwrites: after all loads, so
+// that none of them is waited for by itself
+__device__ __forceinline__ void adj_drop(const GatherRows& g, const XSide& xs, float* Lr, float* Lb)
+{
+    if (g.mz) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            if (kCZ[i] >= 0) continue;
+            const bool my = kCY[i] != 0 && g.my[kCY[i] > 0];
+            if (!my && xs.inlet && !(kCX[i] > 0 ? xs.wp : (kCX[i] < 0 && xs.wm))) Lr[i] = Lb[i] = 0.f;
         }
-        Lr[I] = vr;
-        Lb[I] = vb;
-        adj_gather<BC, I + 1>(k, lam, ML, nd, Lr, Lb);
+    }
+    if (g.lost[2]) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            if (kCZ[i] > 0 || (kCZ[i] == 0 && g.lost[1])) Lr[i] = Lb[i] = 0.f;
     }
 }
 
-template <int BC>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj_node(
+// 783 -> 540 us on the 128x128x512 jet (460 would be the traffic of 340 B per node).
+// It was bound by its arithmetic at two waves per SIMD, 3600 vector instructions per
+// wave on 256 registers: per-lane 64-bit addresses, mirrored directions by selects per
+// lane, the node map direction by direction.  Rows by scalars and the node map by
+// opposite pairs leave 2000 (620 us), by moments 1570 on 141 registers (590 us), which
+// three waves per SIMD hold (540 us; four spill).  The loads go out before the
+// window's barrier: 130 us slower with the window first.
+template <int BC, class TL>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_adj_node(
     const float* __restrict__ MOM, const float* __restrict__ lam_in, const float* __restrict__ ML,
     const float2* __restrict__ PD, const float* __restrict__ XR, float* __restrict__ LC, float4* __restrict__ AG0,
     float4* __restrict__ AG1, double* __restrict__ AP, KP k)
 {
-    // the (phi, rho) stencil from the caches: an LDS window with its barrier
-    // measured slower at this kernel's two waves per SIMD
-    const Node nd = this_node(k);
+    constexpr int TX = TL::CX, TY = TL::CY;
+    __shared__ float2 win[TileShape<TX, TY>::W];
+    const Tile t = this_tile<TX, TY>(k);
+    const Node& nd = t.nd;
     double acc[1] = {0.0};
+    // all global loads before the barrier of the window; lanes and blocks beyond the
+    // lattice repeat its last nodes
+    const size_t N = k.N;
+    const int y = min(t.y0 + t.ly, k.ny - 1), z = min(t.z, k.nz - 1), x = min(nd.x, k.nx - 1);
+    const size_t row = ((size_t)z * k.ny + y) * (uint32_t)k.nx;
+    float Lr[Q], Lb[Q];
+    XSide xs;
+    xs.p = x + 1;
+    xs.m = x - 1;
+    xs.wp = x == k.nx - 1;
+    xs.wm = x == 0;
+    xs.inlet = BC == LBM_BC_JET && z == 0 && inlet_inside(k, x, y);
+    if (BC == LBM_BC_PERIODIC) {
+        if (xs.wp) xs.p = 0;
+        if (xs.wm) xs.m = k.nx - 1;
+    }
+    const GatherRows rows = gather_rows<BC>(k, lam_in, ML, y, z);
+    adj_gather<BC>(rows, x, xs, Lr, Lb);
+    MomT<float> M;
+    const float* mom = MOM + row;
+    M.m0 = ldp(mom, (uint32_t)x);
+    for (int a = 0; a < 3; ++a) M.j[a] = ldp(mom + (size_t)(1 + a) * N, (uint32_t)x);
+    for (int a = 0; a < 6; ++a) M.P[a] = ldp(mom + (size_t)(4 + a) * N, (uint32_t)x);
+    float xr = ldp(XR, nidx_of(k, x, y, z));
+    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return pd_at<BC, true>(k, PD, x, y, z); },
+                         [&](int x, int y, int z) { return pd_at<BC>(k, PD, x, y, z); },
+                         [&](int w, const float2& v) { win[w] = v; });
+    __syncthreads();
     if (nd.valid) {
+        if (BC == LBM_BC_JET) adj_drop(rows, xs, Lr, Lb);
+        if (k.xr_tagged) xr = frac_of(xr, 0u);
+        double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        gradients_win<TX, TY>(win, t.lx, t.ly, g);
         NodeFwdT<float> f;
-        float xr;
-        adj_node_fwd<BC>(k, MOM, PD, XR, nd, f, xr);
-        float Lr[Q], Lb[Q];
-        adj_gather<BC>(k, lam_in, ML, nd, Lr, Lb);
+        node_fwd<float>(k, M, win[wslot<TX, TY>(t.lx, t.ly, 0, 0, 0)].x, g, f);
         NodeAdjT<float> o;
         node_vjp<float>(k, f, xr, Lr, Lb, o);
-        const size_t N = k.N;
-        const uint32_t n = nidx(k, nd.x, nd.y, nd.z);
         const float lc[10] = {o.Lm0, o.Lj[0], o.Lj[1], o.Lj[2], o.Lq[0], o.Lq[1], o.Lq[2], o.Lq[3], o.Lq[4], o.Lq[5]};
+        float* lcr = LC + row;
 #pragma unroll
-        for (int a = 0; a < 10; ++a) LC[(size_t)a * N + n] = lc[a];
-        const uint32_t pn = pidx(k, nd.x, nd.y, nd.z);
+        for (int a = 0; a < 10; ++a) stp(lcr + (size_t)a * N, (uint32_t)x, lc[a]);
+        const uint32_t pn = pidx(k, x, y, z);
         stp(AG0, pn, make_float4(o.Lgp[0], o.Lgp[1], o.Lgp[2], o.Lphic));
         stp(AG1, pn, make_float4(o.Lgr[0], o.Lgr[1], o.Lgr[2], o.Lxr));
         acc[0] = (double)o.LA;
@@ -344,37 +448,55 @@ __global__ __launch_bounds__(BLOCK) void k_adj_ghosts(float4* __restrict__ AG0, 
     AG1[gi] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// 5. transpose of the gradient stencil and the red / blue cotangents
-template <int BC>
+// 5. transpose of the gradient stencil and the red / blue cotangents.  300 B of
+// traffic per node, two thirds of it the 54 stores; NT (the cotangents do not fit the
+// memory-side cache): non-temporal ones.  665 -> 540 us on the 128x128x512 jet with
+// 24 instead of 32 B per window node, the node's own loads before the barrier and the
+// stores' rows in scalar registers.
+template <int BC, class TL, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_adj_fields(const float4* __restrict__ AG0, const float4* __restrict__ AG1,
                                                        const float2* __restrict__ GH, const float2* __restrict__ PD,
                                                        const float* __restrict__ XR, const float* __restrict__ DL,
                                                        const float* __restrict__ LC, float* __restrict__ lam_out, KP k)
 {
-    // the stencil cotangents of the tile and its rim from LDS windows
-    constexpr int W = TileShape<STX, STY>::W;
-    __shared__ float4 w0[W], w1[W];
-    const Tile t = this_tile<STX, STY>(k);
+    // the stencil cotangents of the tile and its rim from LDS windows, without the
+    // fourth components, which only the node itself reads: 24 B per node, four blocks
+    // per CU instead of three
+    constexpr int TX = TL::CX, TY = TL::CY, W = TileShape<TX, TY>::W;
+    __shared__ float2 w0[W], w1[W], w2[W];
+    const Tile t = this_tile<TX, TY>(k);
     const Node& nd = t.nd;
+    // the node's own values before the barrier of the window; lanes and blocks beyond
+    // the lattice repeat its last nodes
+    const size_t N = k.N;
+    const int y = min(t.y0 + t.ly, k.ny - 1), z = min(t.z, k.nz - 1), x = min(nd.x, k.nx - 1);
+    const uint32_t q0 = (uint32_t)y * (uint32_t)k.nx, nn = nidx_of(k, x, y, z), pn = pidx(k, x, y, z);
+    const size_t row = (size_t)z * k.plane + q0;
+    const float* lcr = LC + row;
+    float lc[10];
+#pragma unroll
+    for (int c = 0; c < 10; ++c) lc[c] = ld_lane(lcr + (size_t)c * N, k.nx, x);
+    const float2 pd = ldp(PD, nn);
+    float xrn = ldp(XR, nn);
+    float Lphi = ldp(AG0, pn).w, Lrf = 0.f;
+    const float Lxr = ldp(AG1, pn).w;
     // batched staging (all loads before the LDS writes): 1.95 -> 1.73 ms per
     // adjoint step on the 128x128x512 jet
-    stage_window<STX, STY>(k, t, [&](int x, int y, int z) { return ldp(AG0, pidx(k, x, y, z)); },
-                           [&](int x, int y, int z) { return ldp(AG0, pidx(k, x, y, z)); },
-                           [&](int w, const float4& v) { w0[w] = v; });
-    stage_window<STX, STY>(k, t, [&](int x, int y, int z) { return ldp(AG1, pidx(k, x, y, z)); },
-                           [&](int x, int y, int z) { return ldp(AG1, pidx(k, x, y, z)); },
-                           [&](int w, const float4& v) { w1[w] = v; });
+    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return ld_cot(AG0, k, x, y, z); },
+                         [&](int x, int y, int z) { return cot_at(AG0, k, x, y, z); },
+                         [&](int w, const float3& v) { w0[w] = make_float2(v.x, v.y); w1[w].x = v.z; });
+    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return ld_cot(AG1, k, x, y, z); },
+                         [&](int x, int y, int z) { return cot_at(AG1, k, x, y, z); },
+                         [&](int w, const float3& v) { w1[w].y = v.x; w2[w] = make_float2(v.y, v.z); });
     __syncthreads();
     if (!nd.valid) return;
-    float Lphi = w0[wslot<STX, STY>(t.lx, t.ly, 0, 0, 0)].w, Lrf = 0.f;
-    const float Lxr = w1[wslot<STX, STY>(t.lx, t.ly, 0, 0, 0)].w;
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
-        const int ws = wslot<STX, STY>(t.lx, t.ly, -kCX[i], -kCY[i], -kCZ[i]);
-        const float4 a0 = w0[ws], a1 = w1[ws];
+        const int ws = wslot<TX, TY>(t.lx, t.ly, -kCX[i], -kCY[i], -kCZ[i]);
+        const float2 a = w0[ws], b = w1[ws], c = w2[ws];
         const float w3 = 3.f * wgt(i);
-        Lphi += w3 * (kCX[i] * a0.x + kCY[i] * a0.y + kCZ[i] * a0.z);
-        Lrf += w3 * (kCX[i] * a1.x + kCY[i] * a1.y + kCZ[i] * a1.z);
+        Lphi += w3 * cdot(i, a.x, a.y, b.x);
+        Lrf += w3 * cdot(i, b.y, c.x, c.y);
     }
     if (BC == LBM_BC_JET) {
         // ghost cells whose mirrored field value is this node's
@@ -393,20 +515,15 @@ __global__ __launch_bounds__(BLOCK) void k_adj_fields(const float4* __restrict__
         }
     }
     // phi = (a - b)/(a + b), a = rho_r/rho_r0, b = rho_b/rho_b0; rho_r/rho; rho
-    const float2 pd = ldp(PD, nd.n);
     const double rho = (double)k.rho_b0 + (double)pd.y;
-    const float xrn = k.xr_tagged ? frac_of(ldp(XR, nd.n), 0u) : ldp(XR, nd.n);
+    if (k.xr_tagged) xrn = frac_of(xrn, 0u);
     const double rr = (double)xrn * rho, rb = rho - rr;
     const double a = rr / (double)k.rho_r0, b = rb / (double)k.rho_b0;
     const double ab2 = (a + b) * (a + b);
     const float Lrr = (float)(Lphi * 2.0 * b / (ab2 * (double)k.rho_r0) + Lrf + Lxr * rb / (rho * rho));
     const float Lrb = (float)(-Lphi * 2.0 * a / (ab2 * (double)k.rho_b0) + Lrf - Lxr * rr / (rho * rho));
-    const size_t N = k.N;
-    const uint32_t n = nidx(k, nd.x, nd.y, nd.z);
-    float lc[10];
-#pragma unroll
-    for (int c = 0; c < 10; ++c) lc[c] = LC[(size_t)c * N + n];
-    const bool top = BC == LBM_BC_JET && nd.z == k.nz - 1;
+    const bool top = BC == LBM_BC_JET && t.z == k.nz - 1;
+    float* out = lam_out + row;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
@@ -419,11 +536,11 @@ __global__ __launch_bounds__(BLOCK) void k_adj_fields(const float4* __restrict__
         if (cy * cz) Ld += (cy * cz) * lc[9];
         float r = Ld + Lrr, bl = Ld + Lrb;
         if (top) {
-            r += DL[(size_t)i * k.plane + nd.q];
-            bl += DL[(size_t)(Q + i) * k.plane + nd.q];
+            r += ldp(DL + (size_t)i * k.plane + q0, (uint32_t)x);
+            bl += ldp(DL + (size_t)(Q + i) * k.plane + q0, (uint32_t)x);
         }
-        lam_out[(size_t)i * N + n] = r;
-        lam_out[(size_t)(Q + i) * N + n] = bl;
+        st_lane<NT>(out + (size_t)i * N, k.nx, x, r);
+        st_lane<NT>(out + (size_t)(Q + i) * N, k.nx, x, bl);
     }
 }
 

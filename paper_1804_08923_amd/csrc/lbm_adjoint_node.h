@@ -111,62 +111,70 @@ CG_HD void node_fwd(const KP& k, const MomT<R>& M, R phic, const double* g, Node
     for (int a = 0; a < 3; ++a) f.n[a] = (R)(g[a] * ign);
 }
 
-// colour-blind post-collision population f'_i of direction I
-template <class R, int I>
-CG_HD R fpost_dir(const KP& k, const NodeFwdT<R>& f, const Basis1T<R>& bx, const Basis1T<R>& by,
-                  const Basis1T<R>& bz, R u2, R uF, R ur)
-{
-    constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
-    constexpr int jx = cx + 1, jy = cy + 1, jz = cz + 1;
-    const R w = (R)wgtd(I);
-    const R cu = cx * f.u[0] + cy * f.u[1] + cz * f.u[2];
-    const R poly = cu * (R(3) + R(4.5) * cu + R(4.5) * cu * cu - R(4.5) * u2) - R(1.5) * u2;
-    R v;
-    if (I == 0) {
-        v = f.rho * f.abar + w * f.rho * poly - R(3) * f.nub * ur - R(1.5) * w * uF;
-        if (f.on) v += (R)k.A * R(10.0 / 27.0) * f.gn;
-    } else {
-        const R cr = cx * f.gr[0] + cy * f.gr[1] + cz * f.gr[2];
-        const R cF = cx * f.F[0] + cy * f.F[1] + cz * f.F[2];
-        const R cn = cx * f.n[0] + cy * f.n[1] + cz * f.n[2];
-        v = w * (f.rho * (f.kap + poly) + R(9) * f.nub * cu * cr + R(4.5) * cu * cF - R(1.5) * uF + R(1.5) * cF);
-        if (f.on) v += (R)k.A * w * f.gn * (cn * cn - R(1));
-    }
-    // relaxed-moment part Delta
-    v += f.kk[3] * bx.h1[jx] * by.h1[jy] * bz.h0[jz] + f.kk[4] * bx.h1[jx] * by.h0[jy] * bz.h1[jz] +
-         f.kk[5] * bx.h0[jx] * by.h1[jy] * bz.h1[jz] + f.kk[0] * h2r<R>(jx) * by.h0[jy] * bz.h0[jz] +
-         f.kk[1] * bx.h0[jx] * h2r<R>(jy) * bz.h0[jz] + f.kk[2] * bx.h0[jx] * by.h0[jy] * h2r<R>(jz);
-    return v;
-}
-
+// Colour-blind post-collision populations f' by opposite pairs (i, i + 1), odd i,
+// which share the parts that are even and odd in c:
+//   even = w [rho kappa - 1.5 rho u^2 - 1.5 u.F - A |g| + cu (4.5 rho cu + 9 nu cr + 4.5 cF) + A |g| (c.n)^2],
+//   odd  = w [cu (rho (3 - 4.5 u^2) + 4.5 rho cu^2) + 1.5 cF]
+// (cu = c.u, cr = c.grad rho, cF = c.F), and the relaxed moments contracted axis by
+// axis (z, y, then x).
 template <class R>
 struct PostCtx {
     Basis1T<R> bx, by, bz;
-    R u2, uF, ur;
-    CG_HD explicit PostCtx(const NodeFwdT<R>& f)
+    R u2, uF, ur, K0, K1, r45, nub9, Ag;
+    R U0[3][3], U1[3][3], U2[3][3];  // [cy + 1][cz + 1]
+    CG_HD explicit PostCtx(const KP& k, const NodeFwdT<R>& f)
         : bx(f.u[0]), by(f.u[1]), bz(f.u[2]),
           u2(f.u[0] * f.u[0] + f.u[1] * f.u[1] + f.u[2] * f.u[2]),
           uF(f.u[0] * f.F[0] + f.u[1] * f.F[1] + f.u[2] * f.F[2]),
           ur(f.u[0] * f.gr[0] + f.u[1] * f.gr[1] + f.u[2] * f.gr[2])
     {
+        Ag = f.on ? (R)k.A * f.gn : R(0);
+        K0 = f.rho * f.kap - R(1.5) * f.rho * u2 - R(1.5) * uF - Ag;
+        K1 = f.rho * (R(3) - R(4.5) * u2);
+        r45 = R(4.5) * f.rho;
+        nub9 = R(9) * f.nub;
+        for (int jz = 0; jz < 3; ++jz) {
+            const R a = f.kk[3] * bz.h0[jz], b = f.kk[4] * bz.h1[jz], c = f.kk[5] * bz.h1[jz];
+            const R d = f.kk[0] * bz.h0[jz], e = f.kk[1] * bz.h0[jz], g = f.kk[2] * h2r<R>(jz);
+            for (int jy = 0; jy < 3; ++jy) {
+                U1[jy][jz] = a * by.h1[jy] + b * by.h0[jy];
+                U0[jy][jz] = c * by.h1[jy] + e * h2r<R>(jy) + g * by.h0[jy];
+                U2[jy][jz] = d * by.h0[jy];
+            }
+        }
+    }
+    CG_HD R delta(int cx, int cy, int cz) const
+    {
+        return U0[cy + 1][cz + 1] * bx.h0[cx + 1] + U1[cy + 1][cz + 1] * bx.h1[cx + 1] +
+               U2[cy + 1][cz + 1] * h2r<R>(cx + 1);
+    }
+    CG_HD R rest(const NodeFwdT<R>& f) const
+    {
+        const R w = (R)wgtd(0);
+        return f.rho * f.abar - R(1.5) * w * f.rho * u2 - R(3) * f.nub * ur - R(1.5) * w * uF + Ag * R(10.0 / 27.0) +
+               delta(0, 0, 0);
+    }
+    // f' of directions i and i + 1
+    CG_HD void pair(int i, const NodeFwdT<R>& f, R& fp, R& fm) const
+    {
+        const R w = (R)wgtd(i);
+        const R cu = cdot(i, f.u[0], f.u[1], f.u[2]), cr = cdot(i, f.gr[0], f.gr[1], f.gr[2]);
+        const R cF = cdot(i, f.F[0], f.F[1], f.F[2]), cn = cdot(i, f.n[0], f.n[1], f.n[2]);
+        const R even = w * (K0 + cu * (r45 * cu + (nub9 * cr + R(4.5) * cF)) + (Ag * cn) * cn);
+        const R odd = w * (cu * (K1 + r45 * (cu * cu)) + R(1.5) * cF);
+        fp = even + odd + delta(kCX[i], kCY[i], kCZ[i]);
+        fm = even - odd + delta(-kCX[i], -kCY[i], -kCZ[i]);
     }
 };
-
-template <class R, int I = 0>
-CG_HD void fpost_all(const KP& k, const NodeFwdT<R>& f, const PostCtx<R>& c, R* fp)
-{
-    if constexpr (I < Q) {
-        fp[I] = fpost_dir<R, I>(k, f, c.bx, c.by, c.bz, c.u2, c.uF, c.ur);
-        fpost_all<R, I + 1>(k, f, c, fp);
-    }
-}
 
 // colour-blind post-collision populations f'_i and the recolouring vector V
 template <class R>
 CG_HD void node_post(const KP& k, const NodeFwdT<R>& f, R xr, R* fp, R* V)
 {
-    const PostCtx<R> c(f);
-    fpost_all<R>(k, f, c, fp);
+    const PostCtx<R> c(k, f);
+    fp[0] = c.rest(f);
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) c.pair(i, f, fp[i], fp[i + 1]);
     const R s = f.on ? (R)k.beta * xr * (R(1) - xr) * f.rho * f.kap : R(0);
     for (int a = 0; a < 3; ++a) V[a] = s * f.n[a];
 }
@@ -183,45 +191,165 @@ CG_HD void recolour_dir(int i, R xr, R fpi, const R* V, R& fr, R& fb)
 
 template <class R>
 struct NodeAdjT {
-    R Lm0, Lj[3], Lq[6];  // cotangents of the raw moments of d: Ld_i = Lm0 + c_i.Lj + c_i c_i : Lq
-    R Ld[Q];          // cotangent of d_i
+    R Lm0, Lj[3], Lq[6];  // cotangents of the raw moments of d (that of d_i is Lm0 + c_i.Lj + c_i c_i : Lq)
     R Lgp[3], Lgr[3]; // of grad phi, grad rho
     R Lphic, Lxr, LA; // of phi at the node, rho_r / rho, A
 };
 
-// first sweep: colour-blind cotangents L'_i = Lb_i + xr (Lr_i - Lb_i) (written
-// over Lb), and the cotangents of xr and V through the recolouring
-template <class R, int I = 0>
-CG_HD void vjp_recolour(const KP& k, const NodeFwdT<R>& f, const PostCtx<R>& c, R xr, const R* Lr, R* L, R& Lxr,
-                        R* LV)
-{
-    if constexpr (I < Q) {
-        const R dl = Lr[I] - L[I];
-        L[I] += xr * dl;
-        Lxr += dl * fpost_dir<R, I>(k, f, c.bx, c.by, c.bz, c.u2, c.uF, c.ur);
-        if (I != 0) {
-            const R s = dl * (R)(wgtd(I) * inv_lend(I));
-            if (kCX[I]) LV[0] += kCX[I] * s;
-            if (kCY[I]) LV[1] += kCY[I] * s;
-            if (kCZ[I]) LV[2] += kCZ[I] * s;
-        }
-        vjp_recolour<R, I + 1>(k, f, c, xr, Lr, L, Lxr, LV);
+// Weighted moments sum_i w_i v_i c_ia c_ib ... up to third order of 27 values, axis by
+// axis (w_i is a product of 1/6, 2/3, 1/6 per axis): 58 operations for the sums that
+// the equilibrium, Phi and the forcing need, 20 per direction one direction at a time.
+template <class R>
+struct WMomT {
+    R m0, m1[3], m2[6];  // m2: xx yy zz xy xz yz
+    R xxy, xxz, xyy, yyz, xzz, yzz, xyz;
+    CG_HD explicit WMomT(const R* v)
+    {
+        R X[3][3][3], Y[3][3][3];  // [order in x][jy][jz], [orders in x and y][jz]
+#pragma unroll
+        for (int jy = 0; jy < 3; ++jy)
+#pragma unroll
+            for (int jz = 0; jz < 3; ++jz)
+                line(v[dir_of(-1, jy - 1, jz - 1)], v[dir_of(0, jy - 1, jz - 1)], v[dir_of(1, jy - 1, jz - 1)],
+                     X[0][jy][jz], X[1][jy][jz], X[2][jy][jz]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int jz = 0; jz < 3; ++jz)
+                line(X[a][0][jz], X[a][1][jz], X[a][2][jz], Y[a][0][jz], Y[a][1][jz], Y[a][2][jz]);
+        const R W = R(1.0 / 216.0);
+        R z[3][3][3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3 - (a == 2); ++b) {
+                line(Y[a][b][0], Y[a][b][1], Y[a][b][2], z[a][b][0], z[a][b][1], z[a][b][2]);
+                for (int c = 0; c < 3; ++c) z[a][b][c] *= W;
+            }
+        m0 = z[0][0][0];
+        m1[0] = z[1][0][0]; m1[1] = z[0][1][0]; m1[2] = z[0][0][1];
+        m2[0] = z[2][0][0]; m2[1] = z[0][2][0]; m2[2] = z[0][0][2];
+        m2[3] = z[1][1][0]; m2[4] = z[1][0][1]; m2[5] = z[0][1][1];
+        xxy = z[2][1][0]; xxz = z[2][0][1]; xyy = z[1][2][0]; yyz = z[0][2][1];
+        xzz = z[1][0][2]; yzz = z[0][1][2]; xyz = z[1][1][1];
     }
+    // sum w v c (c.a)
+    CG_HD void second(const R* a, R* o) const
+    {
+        o[0] = m2[0] * a[0] + m2[3] * a[1] + m2[4] * a[2];
+        o[1] = m2[3] * a[0] + m2[1] * a[1] + m2[5] * a[2];
+        o[2] = m2[4] * a[0] + m2[5] * a[1] + m2[2] * a[2];
+    }
+    // sum w v c (c.a)^2
+    CG_HD void third(const R* a, R* o) const
+    {
+        const R x2 = R(2) * a[0], y2 = R(2) * a[1], xx = a[0] * a[0], yy = a[1] * a[1], zz = a[2] * a[2];
+        const R xy = x2 * a[1], xz = x2 * a[2], yz = y2 * a[2];
+        o[0] = m1[0] * xx + xxy * xy + xxz * xz + xyy * yy + xzz * zz + xyz * yz;
+        o[1] = m1[1] * yy + xyy * xy + yyz * yz + xxy * xx + yzz * zz + xyz * xz;
+        o[2] = m1[2] * zz + xzz * xz + yzz * yz + xxz * xx + yyz * yy + xyz * xy;
+    }
+
+private:
+    static CG_HD void line(R v0, R v1, R v2, R& a, R& b, R& c)
+    {
+        c = v0 + v2;
+        b = v2 - v0;
+        a = c + R(4) * v1;
+    }
+};
+template <class R>
+CG_HD R dot3(const R* a, const R* b)
+{
+    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-// reverse sweep of the node map.  Lr: cotangents of the red post-collision
-// populations; LbL: on entry those of the blue ones, overwritten.
+// (sum v h0, sum v h1, sum v h2) over c = -1, 0, 1 of the inverse central-moment basis
 template <class R>
-CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, const R* Lr, R* LbL, NodeAdjT<R>& o)
+CG_HD void basis_line(R u, R v0, R v1, R v2, R& a, R& b, R& c)
+{
+    c = R(0.5) * (v0 + v2) - v1;
+    const R t = R(0.5) * (v2 - v0) + u * c;
+    a = v1 + u * t;
+    b = t + u * c;
+}
+// [a][b][jz]: 27 values contracted with the bases of x and y
+template <class R>
+CG_HD void basis_xy(const R* u, const R* v, R (&Y)[3][3][3])
+{
+    R X[3][3][3];
+#pragma unroll
+    for (int jy = 0; jy < 3; ++jy)
+#pragma unroll
+        for (int jz = 0; jz < 3; ++jz)
+            basis_line(u[0], v[dir_of(-1, jy - 1, jz - 1)], v[dir_of(0, jy - 1, jz - 1)],
+                       v[dir_of(1, jy - 1, jz - 1)], X[0][jy][jz], X[1][jy][jz], X[2][jy][jz]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int jz = 0; jz < 3; ++jz)
+            basis_line(u[1], X[a][0][jz], X[a][1][jz], X[a][2][jz], Y[a][0][jz], Y[a][1][jz], Y[a][2][jz]);
+}
+template <class R>
+CG_HD R basis_z(R u, const R (&Y)[3][3][3], int a, int b, int c)
+{
+    R z[3];
+    basis_line(u, Y[a][b][0], Y[a][b][1], Y[a][b][2], z[0], z[1], z[2]);
+    return z[c];
+}
+
+// reverse sweep of the node map.  Lr, LbL: on entry the cotangents of the red and blue
+// post-collision populations; both are overwritten.
+template <class R>
+CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, R* Lr, R* LbL, NodeAdjT<R>& o)
 {
     const R rho = f.rho, nub = f.nub;
     const R* u = f.u;
     const R* F = f.F;
     const R* gr = f.gr;
-    const PostCtx<R> pc(f);
+    const R* n = f.n;
+    const R u2 = dot3(u, u), uF = dot3(u, F), ur = dot3(u, gr);
+    const R K1 = R(3) - R(4.5) * u2, w0 = (R)wgtd(0);
     R* L = LbL;
-    R Lxr = 0, LV[3] = {0, 0, 0};
-    vjp_recolour<R>(k, f, pc, xr, Lr, L, Lxr, LV);
+    // recolouring: with D_i = Lr_i - Lb_i (written over Lr) the colour-blind cotangents
+    // L'_i = Lb_i + xr D_i (over Lb), that of xr, sum_i D_i f'_i, and of V
+    R LV[3] = {0, 0, 0};
+    Lr[0] -= L[0];
+    L[0] += xr * Lr[0];
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+        const R dp = Lr[i] - L[i], dm = Lr[i + 1] - L[i + 1];
+        Lr[i] = dp;
+        Lr[i + 1] = dm;
+        L[i] += xr * dp;
+        L[i + 1] += xr * dm;
+        const R s = (dp - dm) * (R)(wgtd(i) * inv_lend(i));
+        if (kCX[i]) LV[0] += kCX[i] * s;
+        if (kCY[i]) LV[1] += kCY[i] * s;
+        if (kCZ[i]) LV[2] += kCZ[i] * s;
+    }
+    R Lxr;
+    {
+        const WMomT<R> D(Lr);
+        R Du[3], Duu[3];
+        D.second(u, Du);
+        D.third(u, Duu);
+        const R Ag = f.on ? (R)k.A * f.gn : R(0), d0 = Lr[0];
+        Lxr = (D.m0 - w0 * d0) * (rho * f.kap - R(1.5) * rho * u2 - R(1.5) * uF - Ag) + rho * K1 * dot3(D.m1, u) +
+              R(1.5) * dot3(D.m1, F) + dot3(Du, u) * (R(4.5) * rho) + R(4.5) * rho * dot3(Duu, u) +
+              R(9) * nub * dot3(Du, gr) + R(4.5) * dot3(Du, F) +
+              d0 * (rho * f.abar - R(1.5) * w0 * rho * u2 - R(3) * nub * ur - R(1.5) * w0 * uF + Ag * R(10.0 / 27.0));
+        if (f.on) {
+            R Dn[3];
+            D.second(n, Dn);
+            Lxr += Ag * dot3(Dn, n);
+        }
+        R Y[3][3][3];
+        basis_xy(u, Lr, Y);
+        Lxr += f.kk[0] * basis_z(u[2], Y, 2, 0, 0) + f.kk[1] * basis_z(u[2], Y, 0, 2, 0) +
+               f.kk[2] * basis_z(u[2], Y, 0, 0, 2) + f.kk[3] * basis_z(u[2], Y, 1, 1, 0) +
+               f.kk[4] * basis_z(u[2], Y, 1, 0, 1) + f.kk[5] * basis_z(u[2], Y, 0, 1, 1);
+    }
     R Lrho = 0, Lkap = 0, Labar = 0, Lnub = 0;
     R Lu[3] = {0, 0, 0}, LF[3] = {0, 0, 0}, Lgr[3] = {0, 0, 0}, Lgp[3] = {0, 0, 0};
     const R beta = (R)k.beta;
@@ -235,33 +363,22 @@ CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, const R* Lr, R* LbL
         const R ig = R(1) / f.gn;
         for (int a = 0; a < 3; ++a) Lgp[a] += sV * (LV[a] - LVn * f.n[a]) * ig;
     }
-    // equilibrium, Phi and forcing terms, direction by direction
-    const R u2 = pc.u2;
-    R su = 0, sA = 0, S0 = 0, M2[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
-        const R a = L[i] * (R)wgtd(i);
-        const R cu = cx * u[0] + cy * u[1] + cz * u[2];
-        Lrho += a * (cu * (R(3) + R(4.5) * cu + R(4.5) * cu * cu - R(4.5) * u2) - R(1.5) * u2);
-        su += a * (R(3) + R(9) * cu);
-        sA += a;
-        if (i != 0) {
-            const R cr = cx * gr[0] + cy * gr[1] + cz * gr[2];
-            const R cF = cx * F[0] + cy * F[1] + cz * F[2];
-            const R cc = a * (rho * (R(3) + R(9) * cu + R(13.5) * cu * cu - R(4.5) * u2) + R(9) * nub * cr +
-                              R(4.5) * cF);
-            const R cg = a * R(9) * nub * cu;
-            const R cf = a * (R(4.5) * cu + R(1.5));
-            if (cx) { Lu[0] += cx * cc; Lgr[0] += cx * cg; LF[0] += cx * cf; M2[0] += a; }
-            if (cy) { Lu[1] += cy * cc; Lgr[1] += cy * cg; LF[1] += cy * cf; M2[1] += a; }
-            if (cz) { Lu[2] += cz * cc; Lgr[2] += cz * cg; LF[2] += cz * cf; M2[2] += a; }
-            Lnub += a * R(9) * cu * cr;
-            S0 += a;
-            if (cx * cy) M2[3] += (cx * cy) * a;
-            if (cx * cz) M2[4] += (cx * cz) * a;
-            if (cy * cz) M2[5] += (cy * cz) * a;
-        }
+    // equilibrium, Phi and forcing terms from the weighted moments of L'
+    const WMomT<R> T(L);
+    R Tu[3], Tuu[3], Tr[3], TF[3];
+    T.second(u, Tu);
+    T.second(gr, Tr);
+    T.second(F, TF);
+    T.third(u, Tuu);
+    const R sA = T.m0, S0 = T.m0 - w0 * L[0];
+    const R T1u = dot3(T.m1, u);
+    R su = R(3) * sA + R(9) * T1u;
+    Lrho += K1 * T1u + R(4.5) * (dot3(Tu, u) + dot3(Tuu, u)) - R(1.5) * u2 * sA;
+    Lnub += R(9) * dot3(Tr, u);
+    for (int a = 0; a < 3; ++a) {
+        Lu[a] += rho * (K1 * T.m1[a] + R(9) * Tu[a] + R(13.5) * Tuu[a]) + R(9) * nub * Tr[a] + R(4.5) * TF[a];
+        Lgr[a] += R(9) * nub * Tu[a];
+        LF[a] += R(4.5) * Tu[a] + R(1.5) * T.m1[a];
     }
     su *= rho;
     for (int c = 0; c < 3; ++c) {
@@ -272,7 +389,7 @@ CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, const R* Lr, R* LbL
     const R L0 = L[0];
     Lrho += f.abar * L0;
     Labar += rho * L0;
-    Lnub += R(-3) * pc.ur * L0;
+    Lnub += R(-3) * ur * L0;
     for (int c = 0; c < 3; ++c) {
         Lu[c] += R(-3) * nub * L0 * gr[c];
         Lgr[c] += R(-3) * nub * L0 * u[c];
@@ -284,44 +401,17 @@ CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, const R* Lr, R* LbL
     R LA = 0;
     if (f.on) {
         const R A = (R)k.A;
-        const R* n = f.n;
-        const R Mn[3] = {M2[0] * n[0] + M2[3] * n[1] + M2[4] * n[2], M2[3] * n[0] + M2[1] * n[1] + M2[5] * n[2],
-                         M2[4] * n[0] + M2[5] * n[1] + M2[2] * n[2]};
+        R Mn[3];
+        T.second(n, Mn);
         const R nMn = n[0] * Mn[0] + n[1] * Mn[1] + n[2] * Mn[2];
         const R b0 = L0 * R(10.0 / 27.0) - S0;
         LA = f.gn * (nMn + b0);
         for (int c = 0; c < 3; ++c) Lgp[c] += A * (R(2) * Mn[c] + (b0 - nMn) * n[c]);
     }
     // relaxed-moment part: C[a][b][c] = sum over directions of L h_a(cx) h_b(cy) h_c(cz)
-    const Basis1T<R>& bx = pc.bx;
-    const Basis1T<R>& by = pc.by;
-    const Basis1T<R>& bz = pc.bz;
-    R X[3][3][3];  // [basis a][jy][jz], contracted over x
-#pragma unroll
-    for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-        for (int jz = 0; jz < 3; ++jz) {
-            const R v0 = L[dir_of(-1, jy - 1, jz - 1)], v1 = L[dir_of(0, jy - 1, jz - 1)],
-                    v2 = L[dir_of(1, jy - 1, jz - 1)];
-            X[0][jy][jz] = v0 * bx.h0[0] + v1 * bx.h0[1] + v2 * bx.h0[2];
-            X[1][jy][jz] = v0 * bx.h1[0] + v1 * bx.h1[1] + v2 * bx.h1[2];
-            X[2][jy][jz] = R(0.5) * (v0 + v2) - v1;
-        }
-    R Y[3][3][3];  // [a][b][jz]
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int jz = 0; jz < 3; ++jz) {
-            const R v0 = X[a][0][jz], v1 = X[a][1][jz], v2 = X[a][2][jz];
-            Y[a][0][jz] = v0 * by.h0[0] + v1 * by.h0[1] + v2 * by.h0[2];
-            Y[a][1][jz] = v0 * by.h1[0] + v1 * by.h1[1] + v2 * by.h1[2];
-            Y[a][2][jz] = R(0.5) * (v0 + v2) - v1;
-        }
-    auto Cz = [&](int a, int b, int c) -> R {
-        const R v0 = Y[a][b][0], v1 = Y[a][b][1], v2 = Y[a][b][2];
-        return c == 0 ? v0 * bz.h0[0] + v1 * bz.h0[1] + v2 * bz.h0[2]
-                      : (c == 1 ? v0 * bz.h1[0] + v1 * bz.h1[1] + v2 * bz.h1[2] : R(0.5) * (v0 + v2) - v1);
-    };
+    R Y[3][3][3];
+    basis_xy(u, L, Y);
+    auto Cz = [&](int a, int b, int c) -> R { return basis_z(u[2], Y, a, b, c); };
     const R C200 = Cz(2, 0, 0), C020 = Cz(0, 2, 0), C002 = Cz(0, 0, 2), C110 = Cz(1, 1, 0), C101 = Cz(1, 0, 1),
             C011 = Cz(0, 1, 1), C210 = Cz(2, 1, 0), C201 = Cz(2, 0, 1), C111 = Cz(1, 1, 1), C120 = Cz(1, 2, 0),
             C102 = Cz(1, 0, 2), C021 = Cz(0, 2, 1), C012 = Cz(0, 1, 2);
@@ -369,18 +459,6 @@ CG_HD void node_vjp(const KP& k, const NodeFwdT<R>& f, R xr, const R* Lr, R* LbL
     }
     Lrho -= (u[0] * Lu[0] + u[1] * Lu[1] + u[2] * Lu[2]) * inv_rho;
     const R Lm0 = Lrho + (R)k.gx * LF[0] + (R)k.gy * LF[1] + (R)k.gz * LF[2];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const int cx = kCX[i], cy = kCY[i], cz = kCZ[i];
-        R v = Lm0;
-        if (cx) v += cx * Lj[0] + Lq[0];
-        if (cy) v += cy * Lj[1] + Lq[1];
-        if (cz) v += cz * Lj[2] + Lq[2];
-        if (cx * cy) v += (cx * cy) * Lq[3];
-        if (cx * cz) v += (cx * cz) * Lq[4];
-        if (cy * cz) v += (cy * cz) * Lq[5];
-        o.Ld[i] = v;
-    }
     o.Lm0 = Lm0;
     for (int a = 0; a < 3; ++a) {
         o.Lj[a] = Lj[a];

@@ -246,18 +246,13 @@ __device__ __forceinline__ void st_row(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
 }
 
 // 16-byte record (R, reference record) of node x of row `row` (uniform)
-#ifndef NTREC
-#define XR2 0
-#else
-#define XR2 (NT ? 2 : 0)
-#endif
 template <bool NT, class T>
 __device__ __forceinline__ void st_rec(T* __restrict__ base, const KP& k, uint32_t row, int x, T v)
 {
     static_assert(sizeof(T) == 16, "16-byte records");
     const auto r = row_rsrc(base + (size_t)row * (uint32_t)k.rs, (uint32_t)k.rs);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) uint32_t, v), r,
-                                           (uint32_t)x * 16u, 0, XR2);
+                                           (uint32_t)x * 16u, 0, 0);
 }
 
 // ---------------------------------------------------------------- 16-bit storage
@@ -1156,22 +1151,22 @@ __device__ __forceinline__ void gradients(const float2* __restrict__ pd, const K
     }
 }
 
-// the same gradients in FP32 from the LDS window of the (phi, rho) fields: each
-// pair difference chi(x + c_i) - chi(x - c_i) is exact for nearly equal values,
-// the weighted sum of 13 of them is well conditioned
-template <int TX, int TY, int I = 1>
-__device__ __forceinline__ void gradients_win(const float2* __restrict__ win, int lx, int ly, float (&g)[6])
+// the same gradients from the LDS window of the (phi, rho) fields, in FP32 in the
+// step: each pair difference chi(x + c_i) - chi(x - c_i) is exact for nearly equal
+// values, the weighted sum of 13 of them is well conditioned
+template <int TX, int TY, class T, int I = 1>
+__device__ __forceinline__ void gradients_win(const float2* __restrict__ win, int lx, int ly, T (&g)[6])
 {
     if constexpr (I < Q) {
         constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
         const float2 a = win[wslot<TX, TY>(lx, ly, cx, cy, cz)];
         const float2 b = win[wslot<TX, TY>(lx, ly, -cx, -cy, -cz)];
-        const float dp = a.x - b.x, dr = a.y - b.y;
-        constexpr float w3 = 3.0f * wgt(I);
+        const T dp = (T)a.x - (T)b.x, dr = (T)a.y - (T)b.y;
+        constexpr T w3 = T(3) * (std::is_same<T, double>::value ? (T)wgtd(I) : (T)wgt(I));
         if (cx) { g[0] += (w3 * cx) * dp; g[3] += (w3 * cx) * dr; }
         if (cy) { g[1] += (w3 * cy) * dp; g[4] += (w3 * cy) * dr; }
         if (cz) { g[2] += (w3 * cz) * dp; g[5] += (w3 * cz) * dr; }
-        gradients_win<TX, TY, I + 2>(win, lx, ly, g);
+        gradients_win<TX, TY, T, I + 2>(win, lx, ly, g);
     }
 }
 
