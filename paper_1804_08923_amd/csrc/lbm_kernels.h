@@ -976,8 +976,9 @@ __device__ __forceinline__ void store_moments(float* __restrict__ MOM, const KP&
 }
 
 // Waves per SIMD the density pass is compiled for: eight for the plain 16-bit
-// forms (177 against 184 us in BF16 on the 128x128x512 jet), the compiler's choice
-// for 512-lane blocks in the others (271 against 281 us in FP32).
+// forms, the compiler's choice for 512-lane blocks in the others (on the 128x128x512
+// jet, in the plane-major layout before the rows: 177 against 184 us in BF16, 281
+// against 271 us in FP32).
 template <class S>
 constexpr int kDensityWaves = (sizeof(typename S::T) == 2 && !S::kEqRef) ? 8 : 2;
 
@@ -985,9 +986,9 @@ constexpr int kDensityWaves = (sizeof(typename S::T) == 2 && !S::kEqRef) ? 8 : 2
 // plane, which k_outlet takes: its branch would double this kernel's
 // register count and halve its occupancy).
 // MOMS (the adjoint step from a snapshot): also the raw moments of the pulled
-// deviations into MOM.  A compile-time switch: the moment code in the step's
-// kernel would raise its registers from 69 to 84 (two blocks per CU instead
-// of three), measured 1.85 -> 3.15 ms on the 256x256x1024 jet.
+// deviations into MOM.  A compile-time switch: the moment code would raise the step's
+// registers (FP32: to 90) and with them lower its waves.  330 us on the 128x128x512
+// jet, 268 B of traffic per node at 6.8 TB/s (518 us in the plane-major layout).
 template <int BC, class S, class TL, bool MOMS = false>
 __global__ __launch_bounds__(TL::DX* TL::DY) __attribute__((amdgpu_waves_per_eu(kDensityWaves<S>, 8))) void k_density(
     const typename S::T* __restrict__ src, float2* __restrict__ PD, float* __restrict__ XR, KP k,

@@ -24,7 +24,7 @@ import sys
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 KERNEL_SOURCES = ("lbm_kernels.h", "lbm_lattice.h")
-Q19_SOURCES = ("lbm_q19.h", "lbm_lattice.h")  # the D3Q19 kernels (k19_*)
+Q19_SOURCES = ("lbm_q19.h", "lbm_kernels.h", "lbm_lattice.h")  # the D3Q19 kernels (k19_*)
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 COPY_BYTES = 1 << 30
 
