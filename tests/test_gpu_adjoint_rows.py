@@ -41,3 +41,19 @@ def test_adjoint_rows(torch, orc, orc_cs, shape, bc):  # noqa: F811
         assert abs(rhs - lhs) <= 2e-6 * scale
     d = _cs_step(orc_cs, prob, st64, 9, dA=1.0, inlet=inlet)
     assert abs(dA - (w64 * d).sum()) <= 2e-6 * np.abs(w64 * d).sum()
+
+
+def test_adjoint_beyond_the_caches(torch, orc):  # noqa: F811
+    """Cotangents that do not fit the memory-side cache are stored past it: a periodic
+    lattice of 40 equal slabs (1.3 M nodes, 283 MB of cotangents) against one slab.
+    The nodes' arithmetic is the same, so they agree to FP32 rounding."""
+    small, slabs = _periodic(64, 64, 8), 40
+    st32, _ = _state(orc, small, seed=3)
+    w32 = np.random.default_rng(4).standard_normal(st32.shape).astype(np.float32)
+    ref, dA, _ = _gpu_adjoint(torch, small, st32, 5, w32)
+    big = _periodic(64, 64, 8 * slabs)
+    lam, dA_big, _ = _gpu_adjoint(torch, big, np.tile(st32, slabs), 5, np.tile(w32, slabs))
+    err = np.abs(lam.reshape(len(ref), slabs, -1) - ref[:, None, :]).max() / np.abs(ref).max()
+    say(f"adjoint of {slabs} equal slabs: max difference {err:.2e}, dJ/dA {dA_big:.9e} against {slabs * dA:.9e}")
+    assert err <= 1e-6
+    assert abs(dA_big - slabs * dA) <= 1e-6 * abs(slabs * dA)
