@@ -393,6 +393,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
         if (k.xr_tagged) xr = frac_of(xr, 0u);
         double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         gradients_win<TX, TY>(win, t.lx, t.ly, g);
+        acc[0] = perturb_vjp(k, g, (double)xr, Lr, Lb);
         NodeFwdT<float> f;
         node_fwd<float>(k, M, win[wslot<TX, TY>(t.lx, t.ly, 0, 0, 0)].x, g, f);
         NodeAdjT<float> o;
@@ -404,7 +405,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
         const uint32_t pn = pidx(k, x, y, z);
         stp(AG0, pn, make_float4(o.Lgp[0], o.Lgp[1], o.Lgp[2], o.Lphic));
         stp(AG1, pn, make_float4(o.Lgr[0], o.Lgr[1], o.Lgr[2], o.Lxr));
-        acc[0] = (double)o.LA;
     }
     block_partials<1>(acc, AP, blockIdx.y * gridDim.x + blockIdx.x);
 }
