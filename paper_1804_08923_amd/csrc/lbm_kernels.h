@@ -711,34 +711,41 @@ struct Tile {
     Node nd;
 };
 
-// Grid of a launch over `planes` planes with T tiles each (see this_tile): (T, planes)
-// where T is a multiple of 8 or below 8, else the blocks of the planes rounded up to a
-// multiple of 8 in one row.
+// Order of the tiles.  Workgroups go round-robin to the 8 XCDs, so a plane's
+// neighbouring tiles would sit on different L2s, each fetching the halo
+// rows they share and each writing a part of the lines in which two
+// unaligned rows meet.  With T tiles in a plane XCD j takes the contiguous
+// band of tiles [(j T + z mod 8) / 8, ((j + 1) T + z mod 8) / 8): T tiles in
+// any eight planes, and where T is a multiple of 8 the same ones in each.
+// Against the plain order where T is no multiple of 8: 0.78 -> 0.70 ms on
+// 154x120x422 nodes (FP32), 0.90 -> 0.78 ms on 144x183x488 (FP16).
+//
+// Grid of a launch over `planes` planes of T tiles: (T, planes) where T is a
+// multiple of 8 or below 8, else the blocks of the planes rounded up to a
+// multiple of 8 in one row.  A row of 2^32 lanes or more cannot be launched (thin
+// lattices: from 2^25 rows of nodes with 128x2 tiles); these keep (T, planes) in the
+// plain order (with more than one plane: a plane has fewer than 2^21 tiles).
+template <int TX, int TY>
+__host__ __device__ __forceinline__ uint32_t tiles_in_plane(int nx, int ny)
+{
+    return (uint32_t)((nx + TX - 1) / TX) * (uint32_t)((ny + TY - 1) / TY);
+}
 template <int TX, int TY>
 inline dim3 tile_grid(int nx, int ny, int planes)
 {
-    const unsigned T = (unsigned)(((nx + TX - 1) / TX) * ((ny + TY - 1) / TY));
-    return T % 8 == 0 || T < 8 ? dim3(T, planes) : dim3(T * (unsigned)((planes + 7) / 8 * 8));
+    const uint64_t T = tiles_in_plane<TX, TY>(nx, ny), row = T * (uint64_t)((planes + 7) / 8 * 8);
+    if (T % 8 == 0 || T < 8 || row * (TX * TY) >= (1ull << 32)) return dim3((unsigned)T, planes);
+    return dim3((unsigned)row);
 }
 
-template <int TX, int TY>
-__device__ __forceinline__ Tile this_tile(const KP& k)
+// tile b and plane z of block (bx, by) of such a grid (gx, gy); false: beyond the planes
+__host__ __device__ __forceinline__ bool tile_of_block(uint32_t gx, uint32_t gy, uint32_t bx, uint32_t by, int T,
+                                                       int planes, int& b, int& z)
 {
-    static_assert(TX % 64 == 0, "a wavefront lies in one row");
-    Tile t;
-    // XCD-aware order: workgroups go round-robin to the 8 XCDs, so a plane's
-    // neighbouring tiles would sit on different L2s, each fetching the halo
-    // rows they share and each writing a part of the lines in which two
-    // unaligned rows meet.  With T tiles in a plane XCD j takes the contiguous
-    // band of tiles [(j T + z mod 8) / 8, ((j + 1) T + z mod 8) / 8): T tiles in
-    // any eight planes, and where T is a multiple of 8 the same ones in each.
-    // Against the plain order where T is no multiple of 8: 0.78 -> 0.70 ms on
-    // 154x120x422 nodes (FP32), 0.90 -> 0.78 ms on 144x183x488 (FP16).
-    const int ntx = (k.nx + TX - 1) / TX;
-    int b = (int)blockIdx.x, z = (int)blockIdx.y;
-    bool live = true;
-    if (gridDim.y == 1 && gridDim.x > 8) {
-        const int T = ntx * ((k.ny + TY - 1) / TY), j = b & 7, i = b >> 3, q = i / T;
+    b = (int)bx;
+    z = (int)by;
+    if (gy == 1 && gx > 8) {
+        const int j = b & 7, i = b >> 3, q = i / T;
         b = i - q * T;  // the band's tiles of planes 8 q .. 8 q + 7, plane by plane
         z = 8 * q;
         int lo = j * T;
@@ -750,10 +757,21 @@ __device__ __forceinline__ Tile this_tile(const KP& k)
             ++z;
         }
         b += lo >> 3;
-        live = z < k.planes;
-    } else if ((gridDim.x & 7u) == 0) {
-        b = (b & 7) * (int)(gridDim.x >> 3) + (b >> 3);
+        return z < planes;
     }
+    if ((gx & 7u) == 0) b = (b & 7) * (int)(gx >> 3) + (b >> 3);
+    return true;
+}
+
+template <int TX, int TY>
+__device__ __forceinline__ Tile this_tile(const KP& k)
+{
+    static_assert(TX % 64 == 0, "a wavefront lies in one row");
+    Tile t;
+    const int ntx = (k.nx + TX - 1) / TX;
+    int b, z;
+    const bool live = tile_of_block(gridDim.x, gridDim.y, blockIdx.x, blockIdx.y,
+                                    (int)tiles_in_plane<TX, TY>(k.nx, k.ny), k.planes, b, z);
     t.z = z + k.z0;
     const int ty = live ? b / ntx : (k.ny + TY) / TY + 1, tx = live ? b - ty * ntx : 0;  // idle: beyond every row
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // uniform, and so are y and the row
