@@ -53,7 +53,8 @@ struct lbm_handle {
     long long t;        // time level of the current state
     int unshifted;      // current buffer holds a general state at the node itself
     dim3 grid_all;      // every interior plane
-    dim3 grid_tiles;    // stencil tiles
+    int form[3];        // of the kernels that read a state node by node (read_form)
+    dim3 grid_read[3];  // and their grids
     dim3 grid_ctiles;   // stencil tiles of the fused collision
     dim3 grid_dtiles;   // stencil tiles of the density pass
     dim3 grid_rows;     // one plane by row segments (outlet)
@@ -75,8 +76,11 @@ namespace {
 
 uint64_t blocks_of(dim3 g) { return (uint64_t)g.x * g.y; }
 
-// partial sums of the FP64 audit: one slot per block of the macroscopic kernel
-uint64_t audit_blocks(const lbm_params* p) { return blocks_of(tile_grid<STX, STY>(p->nx, p->ny, p->nz)); }
+// planes of 256-node blocks
+dim3 node_grid(const lbm_params* p)
+{
+    return dim3((unsigned)(((uint64_t)p->nx * p->ny + BLOCK - 1) / BLOCK), p->nz);
+}
 
 thread_local char g_err[512] = "";
 
@@ -295,18 +299,32 @@ int dispatch(int bc, int storage, F&& f)
     return f(IntC<LBM_BC_JET>{}, StF16Eq{});
 }
 
-// Which tiles the step kernels take: rows of 128 nodes, or rows of 64 where the
+// Which tiles the kernels take: rows of 128 nodes, or rows of 64 where the
 // wavefronts of a row then have a fifth fewer lanes (nx of 1..64 and 129..192).
-// Measured, narrow against wide, FP32: 154x120x422 674 against 713 us, 48x50x190
+// Measured, narrow against wide, FP32 steps: 154x120x422 674 against 713 us, 48x50x190
 // 44 against 52 us; 309x222x205 (a sixth fewer lanes) 1193 against 1170 us,
 // 100x100x100 (none fewer) 71 against 68 us.  The referenced 16-bit forms have
-// tiles of their own (see RefWin).
-enum { TILES_WIDE, TILES_NARROW };
-int step_tiles(const lbm_params* p)
+// step tiles of their own (see RefWin).
+enum { TILES_WIDE, TILES_NARROW, TILES_NONE };
+int row_tiles(const lbm_params* p)
 {
     const int wide = (p->nx + 127) / 128 * 128, narrow = (p->nx + 63) / 64 * 64;
     return 4 * wide > 5 * narrow ? TILES_NARROW : TILES_WIDE;
 }
+
+// TILES_NONE, blocks of consecutive nodes (NodeBlocks), where a row of nx nodes fills
+// less than `share` sixteenths of its tiles' lanes: those read through the caches, with
+// an address per lane, but no lane is idle.
+int tiles_or_nodes(const lbm_params* p, int share)
+{
+    const int tiles = row_tiles(p), w = tiles == TILES_WIDE ? 128 : 64, lanes = (p->nx + w - 1) / w * w;
+    return 16 * p->nx < share * lanes ? TILES_NONE : tiles;
+}
+
+// Step kernels.  D3Q27 steps keep their tiles on every row.  D3Q19, by tiles against by
+// nodes: 16x128x512 149 against 69 us, 24x128x2000 600 against 507, 40x128x2000 705
+// against 767, 72x200x1000 1074 against 1126.
+int step_tiles(const lbm_params* p) { return is_q19(p) ? tiles_or_nodes(p, 9) : row_tiles(p); }
 
 // call f(tiles)
 template <class S, class F>
@@ -320,12 +338,44 @@ int with_tiles(int tiles, F&& f)
     }
 }
 
-// tiles of the adjoint kernels, whatever the storage of the state
-dim3 adjoint_grid(const lbm_params* p)
+// call f(tiles) of a form
+template <class F>
+int with_form(int form, F&& f)
 {
-    return step_tiles(p) == TILES_WIDE ? tile_grid<WideTiles::CX, WideTiles::CY>(p->nx, p->ny, p->nz)
-                                       : tile_grid<NarrowTiles::CX, NarrowTiles::CY>(p->nx, p->ny, p->nz);
+    if (form == TILES_NONE) return f(NodeBlocks{});
+    return with_tiles<StF32>(form, f);
 }
+
+// grid of a form: 256 threads a block, every plane
+dim3 form_grid(const lbm_params* p, int form)
+{
+    if (form == TILES_NONE) return node_grid(p);
+    return form == TILES_WIDE ? tile_grid<WideTiles::CX, WideTiles::CY>(p->nx, p->ny, p->nz)
+                              : tile_grid<NarrowTiles::CX, NarrowTiles::CY>(p->nx, p->ny, p->nz);
+}
+
+// Form of the kernels that read a state node by node, by tiles against by nodes:
+//   fields  FP32 24x128x2000 373 against 274 us, 40x128x2000 386 against 446, 72x200x1000
+//           609 against 617; D3Q19 40x128x2000 358 against 341, 80x200x900 518 against
+//           471, 96x100x400 130 against 132;
+//   state   16x128x512 133 against 111 us (FP32), 124 against 92 (FP16), 65 against 45
+//           (D3Q19), 24x128x2000 560 against 558, 550 against 535, 401 against 370;
+//   diagnostics (all passes; by nodes without the runs along x) 8x128x1024 2470 against
+//           1058 us, 20x128x409 1120 against 1915.
+// On rows that fill their tiles badly the plane-major layout before the rows read the
+// fields alone up to a fifth faster (FP32 below 40 nodes, D3Q19 below 100).
+enum { READ_FIELDS, READ_STATE, READ_DIAG };
+int read_form(const lbm_params* p, int what)
+{
+    const bool fp32 = p->storage == LBM_STORAGE_FP32 && !is_q19(p);
+    return tiles_or_nodes(p, what == READ_FIELDS ? (is_q19(p) ? 11 : 9) : what == READ_STATE ? (fp32 ? 6 : 8) : 4);
+}
+
+// partial sums of the FP64 audit: one slot per block of the macroscopic kernel
+uint64_t audit_blocks(const lbm_params* p) { return blocks_of(form_grid(p, read_form(p, READ_FIELDS))); }
+
+// tiles of the adjoint kernels, whatever the storage of the state
+dim3 adjoint_grid(const lbm_params* p) { return form_grid(p, row_tiles(p)); }
 
 bool aligned(const void* ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
@@ -475,12 +525,20 @@ int lbm_init(lbm_handle** h, const lbm_params* p, const lbm_buffers* buf, const 
     const unsigned bx = (H->k.plane + BLOCK - 1) / BLOCK;
     H->grid_all = dim3(bx, p->nz);
     H->grid_plane = dim3(bx, 1);
-    H->grid_tiles = tile_grid<STX, STY>(p->nx, p->ny, p->nz);
+    for (int r = 0; r < 3; ++r) {
+        H->form[r] = read_form(p, r);
+        H->grid_read[r] = form_grid(p, H->form[r]);
+    }
     H->tiles = step_tiles(p);
     dispatch(p->bc, p->storage, [&](auto, auto st) -> int {
+        const int below = p->bc == LBM_BC_JET ? p->nz - 1 : p->nz;  // the outlet plane has its own kernel
+        if (H->tiles == TILES_NONE) {
+            H->grid_ctiles = node_grid(p);
+            H->grid_dtiles = dim3(H->grid_ctiles.x, below);
+            return LBM_OK;
+        }
         return with_tiles<decltype(st)>(H->tiles, [&](auto tl) -> int {
             using T = decltype(tl);
-            const int below = p->bc == LBM_BC_JET ? p->nz - 1 : p->nz;  // the outlet plane has its own kernel
             H->grid_ctiles = tile_grid<T::CX, T::CY>(p->nx, p->ny, p->nz);
             H->grid_dtiles = tile_grid<T::DX, T::DY>(p->nx, p->ny, below);
             return LBM_OK;
@@ -554,7 +612,7 @@ int q19_launch(lbm_handle* h, const StateSet& dst_set, hipEvent_t* e)
         kd.planes -= 1;
     }
     if (e) HIP_CHECK(hipEventRecord(e[1], h->stream));
-    return with_tiles<StF32>(h->tiles, [&](auto tl) -> int {
+    return with_form(h->tiles, [&](auto tl) -> int {
         using TL = decltype(tl);
         hipLaunchKernelGGL((q19::k19_density<GEN, BC, TL>), h->grid_dtiles, dim3(TL::DX * TL::DY), 0, h->stream, src,
                            h->F2, kd);
@@ -660,6 +718,15 @@ int step_once(lbm_handle* h, const StateSet& dst_set, int dst_cs)
     });
 }
 
+// D3Q19: call f(general form, boundary kind) for reading the current state
+template <class F>
+int q19_state(const lbm_handle* h, F&& f)
+{
+    if (h->unshifted) return f(std::true_type{}, IntC<LBM_BC_PERIODIC>{});
+    if (h->p.bc == LBM_BC_JET) return f(std::false_type{}, IntC<LBM_BC_JET>{});
+    return f(std::false_type{}, IntC<LBM_BC_PERIODIC>{});
+}
+
 // the snapshot at snap, checked for alignment
 int snap_set(const lbm_handle* h, const void* snap, StateSet* s)
 {
@@ -742,30 +809,25 @@ int lbm_macroscopic(lbm_handle* h, float* rho_r, float* rho_b, float* u, float* 
 {
     if (!h) return fail(LBM_ERR_STATE, "handle is NULL");
     const KP k = read_kp(h);
-    int rc = h->q19 ? [&]() -> int {
-        const float* pop = (const float*)cur_set(h).pop;
-        const float* hist = cur_set(h).hist;
-        double* part = audit ? h->audit : nullptr;
-        const bool jet = h->p.bc == LBM_BC_JET;
-        if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_macro<true, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
-                               hist, k, rho_r, rho_b, u, phi, part);
-        else if (jet)
-            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_JET>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop, hist,
-                               k, rho_r, rho_b, u, phi, part);
-        else
-            hipLaunchKernelGGL((q19::k19_macro<false, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
-                               hist, k, rho_r, rho_b, u, phi, part);
-        LAUNCH_CHECK();
-        return LBM_OK;
-    }() : dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
-        using S = decltype(st);
-        constexpr int BC = decltype(bc)::value;
-        hipLaunchKernelGGL((k_macro<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                           (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, rho_r, rho_b, u, phi,
-                           audit ? h->audit : nullptr);
-        LAUNCH_CHECK();
-        return LBM_OK;
+    double* part = audit ? h->audit : nullptr;
+    const dim3 grid = h->grid_read[READ_FIELDS];
+    const int rc = with_form(h->form[READ_FIELDS], [&](auto tl) -> int {
+        using TL = decltype(tl);
+        if (h->q19)
+            return q19_state(h, [&](auto gen, auto bc) -> int {
+                hipLaunchKernelGGL((q19::k19_macro<decltype(gen)::value, decltype(bc)::value, TL>), grid, dim3(BLOCK), 0,
+                                   h->stream, (const float*)cur_set(h).pop, cur_set(h).hist, k, rho_r, rho_b, u, phi,
+                                   part);
+                LAUNCH_CHECK();
+                return LBM_OK;
+            });
+        return dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
+            using S = decltype(st);
+            hipLaunchKernelGGL((k_macro<decltype(bc)::value, S, TL>), grid, dim3(BLOCK), 0, h->stream,
+                               (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, rho_r, rho_b, u, phi, part);
+            LAUNCH_CHECK();
+            return LBM_OK;
+        });
     });
     if (rc != LBM_OK || !audit) return rc;
     double* tot = h->audit + (size_t)h->naud * 5;
@@ -783,28 +845,23 @@ int lbm_get_state(lbm_handle* h, float* state)
     if (!h) return fail(LBM_ERR_STATE, "handle is NULL");
     if (!state) return fail(LBM_ERR_INVALID_ARG, "state is NULL");
     const KP k = read_kp(h);
-    if (h->q19) {
-        const float* pop = (const float*)cur_set(h).pop;
-        const float* hist = cur_set(h).hist;
-        if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_get_state<true, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                               pop, hist, k, state);
-        else if (h->p.bc == LBM_BC_JET)
-            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_JET>), h->grid_tiles, dim3(BLOCK), 0, h->stream, pop,
-                               hist, k, state);
-        else
-            hipLaunchKernelGGL((q19::k19_get_state<false, LBM_BC_PERIODIC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                               pop, hist, k, state);
-        LAUNCH_CHECK();
-        return LBM_OK;
-    }
-    return dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
-        using S = decltype(st);
-        constexpr int BC = decltype(bc)::value;
-        hipLaunchKernelGGL((k_get_state<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                           (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, state, (double)h->k.rho_b0);
-        LAUNCH_CHECK();
-        return LBM_OK;
+    const dim3 grid = h->grid_read[READ_STATE];
+    return with_form(h->form[READ_STATE], [&](auto tl) -> int {
+        using TL = decltype(tl);
+        if (h->q19)
+            return q19_state(h, [&](auto gen, auto bc) -> int {
+                hipLaunchKernelGGL((q19::k19_get_state<decltype(gen)::value, decltype(bc)::value, TL>), grid, dim3(BLOCK),
+                                   0, h->stream, (const float*)cur_set(h).pop, cur_set(h).hist, k, state);
+                LAUNCH_CHECK();
+                return LBM_OK;
+            });
+        return dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
+            using S = decltype(st);
+            hipLaunchKernelGGL((k_get_state<decltype(bc)::value, S, TL>), grid, dim3(BLOCK), 0, h->stream,
+                               (const typename S::T*)cur_set(h).pop, cur_set(h).hist, k, state, (double)h->k.rho_b0);
+            LAUNCH_CHECK();
+            return LBM_OK;
+        });
     });
 }
 
@@ -1025,23 +1082,30 @@ int diag_run(lbm_handle* h, void* work, lbm_jet_stats* stats, int64_t* volumes, 
 {
     const KP k = read_kp(h);
     const DiagWork w = diag_layout(work, k.N);
-    int rc = dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
-        using S = decltype(st);
-        constexpr int BC = decltype(bc)::value;
+    const dim3 grid = h->grid_read[READ_DIAG];
+    int rc = with_form(h->form[READ_DIAG], [&](auto tl) -> int {
+        using TL = decltype(tl);
         hipLaunchKernelGGL(k_diag_clear, dim3(1), dim3(64), 0, h->stream, w);
         LAUNCH_CHECK();
         const float* hist = cur_set(h).hist;
-        if (!h->q19)
-            hipLaunchKernelGGL((k_diag_init<BC, S>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                               (const typename S::T*)cur_set(h).pop, hist, k, w);
-        else if (h->unshifted)
-            hipLaunchKernelGGL((q19::k19_diag_init<true, BC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                               (const float*)cur_set(h).pop, hist, k, w);
+        int r;
+        if (h->q19)
+            r = q19_state(h, [&](auto gen, auto bc) -> int {
+                hipLaunchKernelGGL((q19::k19_diag_init<decltype(gen)::value, decltype(bc)::value, TL>), grid, dim3(BLOCK),
+                                   0, h->stream, (const float*)cur_set(h).pop, hist, k, w);
+                LAUNCH_CHECK();
+                return LBM_OK;
+            });
         else
-            hipLaunchKernelGGL((q19::k19_diag_init<false, BC>), h->grid_tiles, dim3(BLOCK), 0, h->stream,
-                               (const float*)cur_set(h).pop, hist, k, w);
-        LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_diag_merge, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
+            r = dispatch(h->p.bc, h->p.storage, [&](auto bc, auto st) -> int {
+                using S = decltype(st);
+                hipLaunchKernelGGL((k_diag_init<decltype(bc)::value, S, TL>), grid, dim3(BLOCK), 0, h->stream,
+                                   (const typename S::T*)cur_set(h).pop, hist, k, w);
+                LAUNCH_CHECK();
+                return LBM_OK;
+            });
+        if (r != LBM_OK) return r;
+        hipLaunchKernelGGL(k_diag_merge<!TL::kFlat>, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();
         hipLaunchKernelGGL(k_diag_flatten, h->grid_all, dim3(BLOCK), 0, h->stream, k, w);
         LAUNCH_CHECK();

@@ -139,23 +139,22 @@ __device__ __forceinline__ void diag_tally(const DiagWork& w, unsigned long long
 // that of rho_r rho_b0 - rho_b rho_r0.  Where the FP32 masses of the density pass
 // leave no doubt about it (their error is below 1e-5) it is taken from them, else
 // from the FP64 sums of lbm_macroscopic.
-template <int BC, class S>
+template <int BC, class S, class TL>
 __global__ __launch_bounds__(BLOCK) void k_diag_init(const typename S::T* __restrict__ src,
                                                       const float* __restrict__ hprev, KP k, DiagWork w)
 {
-    __shared__ float4 win[TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
+    __shared__ float4 win[kRecWin<TL>];
+    const Tile t = state_tile<BC, TL>(k, win);
     const Node& nd = t.nd;
-    stage_records<BC>(k, t, win);
     bool fg = false;
     const int i = (int)((uint32_t)nd.z * k.plane + nd.q);
     if (nd.valid) {
         bool sure = false;
-        if (!k.unshifted && !(BC == LBM_BC_JET && nd.z == k.nz - 1)) {
+        if (!TL::kFlat && !k.unshifted && !(BC == LBM_BC_JET && nd.z == k.nz - 1)) {
             float d[Q], unused[Q], m0 = 0.f, x0 = 0.f, cf = 0.f, cv = 0.f;
             uint32_t bl = 0;
             pull_dirs<BC, S, false>(src, k, nd.x, nd.y, nd.z, x_offsets<BC, typename S::T>(k, nd.x), d, unused, unused);
-            accum_density_win<STX, STY, false>(k, d, win, t.lx, t.ly, m0, x0, bl, cf, cv);
+            accum_density_win<TL::CX, TL::CY, false>(k, d, win, t.lx, t.ly, m0, x0, bl, cf, cv);
             const float rho = k.rho_b0 + m0, mk = x0 * rho + (cf + (bl ? -cv : cv));
             const float a = (bl ? rho - mk : mk) * k.rho_b0, b = (bl ? mk : rho - mk) * k.rho_r0;
             sure = fabsf(a - b) > 1e-3f * (a + b) && a + b > 0.f;
@@ -163,20 +162,21 @@ __global__ __launch_bounds__(BLOCK) void k_diag_init(const typename S::T* __rest
         }
         if (!sure) {
             double m0, rr, rb, j[3];
-            node_masses<BC, S>(src, k, hprev, t, win, m0, rr, rb, j);
+            node_masses<BC, S, TL>(src, k, hprev, t, win, m0, rr, rb, j);
             const double a = rr / k.rho_r0, b = rb / k.rho_b0;
             fg = (float)((a - b) / (a + b)) > 0.f;  // phi as lbm_macroscopic returns it
         }
     }
     const unsigned long long m = __ballot(fg);
-    const int run = diag_run_label(m, i);
+    const int run = TL::kFlat ? i : diag_run_label(m, i);
     if (nd.valid) w.label[i] = fg ? run : -1;
     diag_tally(w, m, fg ? nd.z : -1);
 }
 
 // 2. union with the face neighbours at -x, -y, -z.  Runs are joined where segments
 // meet; towards -y and -z one union is enough for nodes whose runs go on side by
-// side.
+// side.  RUNS: the labels are runs (else every node has its own).
+template <bool RUNS>
 __global__ __launch_bounds__(BLOCK) void k_diag_merge(KP k, DiagWork w)
 {
     const Node nd = this_node(k);
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(BLOCK) void k_diag_merge(KP k, DiagWork w)
     const int i = (int)((uint32_t)nd.z * k.plane + nd.q);
     if (diag_load(w.label + i) < 0) return;
     const int walk = (int)k.N;
-    const bool begins = (nd.x & 63) == 0;
+    const bool begins = !RUNS || (nd.x & 63) == 0;
     const bool left = nd.x > 0 && w.label[i - 1] >= 0;
     if (left && begins) diag_unite(w.label, i, i - 1, walk, &w.hdr->overflow);
     const auto join = [&](int o) {

@@ -425,9 +425,10 @@ __device__ __forceinline__ XOff x_offsets(const KP& k, int x)
 // inflow).  The jet's outlet plane is never pulled into; its row above is clamped
 // to stay inside the buffer.
 template <int BC, int CY, int CZ>
-__device__ __forceinline__ uint32_t group_row(const KP& k, int y, int z, bool& my)
+__device__ __forceinline__ void group_source(const KP& k, int y, int z, int& ys, int& zs, bool& my)
 {
-    int ys = y - CY, zs = z - CZ;
+    ys = y - CY;
+    zs = z - CZ;
     my = false;
     if (BC == LBM_BC_PERIODIC) {
         if (CY) ys = wrapc(ys, k.ny);
@@ -439,27 +440,35 @@ __device__ __forceinline__ uint32_t group_row(const KP& k, int y, int z, bool& m
         }
         if (CZ < 0 && zs >= k.nz) zs = k.nz - 1;
     }
-    return row_of(k, ys, zs);
 }
 
-// element offset of the group in its row; a mirrored row gives the mirrored group
-template <int BC, int SL, int CY, int CZ>
-__device__ __forceinline__ size_t group_off(const KP& k, int y, int z)
+// Element x (a byte offset) of a row of SL slots of rs elements, counted from slot g
+// of row (y, z).  ROW: the row is uniform over the wavefront; else each lane has its
+// own.
+template <int SL, bool ROW, class T>
+__device__ __forceinline__ T ld_slot(const T* __restrict__ base, const KP& k, int y, int z, int g, uint32_t x)
 {
-    bool my;
-    const uint32_t row = group_row<BC, CY, CZ>(k, y, z, my);
-    const int g = 9 * (CZ + 1) + 3 * (CY + 1) - (my ? 6 * CY : 0);
-    return ((size_t)row * SL + g) * (uint32_t)k.rs;
+    const T* row = base + ((size_t)row_of(k, y, z) * SL + g) * (uint32_t)k.rs;
+    if constexpr (!ROW)
+        return *(const T*)((const char*)row + x);
+    else if constexpr (sizeof(T) == 16)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(row_rsrc(row, (uint32_t)k.rs), x, 0, 0));
+    else
+        return ld_row<T>(row_rsrc(row, 3u * (uint32_t)k.rs), x, 0u);
 }
 
-// stored value of direction I pulled into node row (y, z), row uniform
-template <int BC, class S, int I>
+// stored value of direction I pulled into node row (y, z); ROW: the row is uniform
+// over the wavefront (else every lane has its own)
+template <int BC, class S, int I, bool ROW = true>
 __device__ __forceinline__ typename S::T pull_raw(const typename S::T* __restrict__ src, const KP& k, int y, int z,
                                                   const XOff& xo)
 {
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
-    const auto r = row_rsrc(src + group_off<BC, kSlots<S>, cy, cz>(k, y, z), 3u * (uint32_t)k.rs);
-    return ld_row<typename S::T>(r, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o), 0u);
+    int ys, zs;
+    bool my;
+    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
+    const int g = 9 * (cz + 1) + 3 * (cy + 1) - (my ? 6 * cy : 0);  // a mirrored row gives the mirrored group
+    return ld_slot<kSlots<S>, ROW>(src, k, ys, zs, g, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
 }
 
 // A per-node record at (x, y, z), which may lie one node outside: wrapped, or
@@ -515,27 +524,31 @@ __device__ __forceinline__ float ref_part(const RefRec& r)
     return wgt(I) * (r.e + r.rho * eq_poly(cu, u2));
 }
 
-// 16-byte record of the source of direction I, row (y, z) uniform; m: the axes it
-// has to be mirrored on
-template <int BC, int I, class T>
+// 16-byte record of the source of direction I; m: the axes it has to be mirrored on
+template <int BC, int I, bool ROW = true, class T>
 __device__ __forceinline__ T pull_rec(const T* __restrict__ base, const KP& k, int y, int z, const XOff& xo, int& m)
 {
     static_assert(sizeof(T) == 16, "16-byte records");
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
+    int ys, zs;
     bool my;
-    const uint32_t row = group_row<BC, cy, cz>(k, y, z, my);
-    const auto r = row_rsrc(base + (size_t)row * (uint32_t)k.rs, (uint32_t)k.rs);
+    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
     m = (BC == LBM_BC_JET && ((cx > 0 && xo.wp) || (cx < 0 && xo.wm)) ? 1 : 0) | (my ? 2 : 0);
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, cx > 0 ? xo.rp : (cx < 0 ? xo.rm : xo.ro), 0, 0));
+    return ld_slot<1, ROW>(base, k, ys, zs, 0, cx > 0 ? xo.rp : (cx < 0 ? xo.rm : xo.ro));
 }
 
 // pre-collision deviation d_I pulled into node (x, y, z)
-template <int BC, class S, int I>
+template <int BC, class S, int I, bool ROW = true>
 __device__ __forceinline__ float pull_dev(const typename S::T* __restrict__ src, const KP& k, int x, int y, int z,
                                           const XOff& xo)
 {
     if constexpr (!S::kEqRef) {
-        return S::dec(pull_raw<BC, S, I>(src, k, y, z, xo));
+        return S::dec(pull_raw<BC, S, I, ROW>(src, k, y, z, xo));
+    } else if constexpr (I == 0 && !ROW) {
+        const uint32_t xB = (uint32_t)x * (uint32_t)sizeof(typename S::T);
+        const uint32_t hi = __builtin_bit_cast(uint16_t, ld_slot<kSlots<S>, false>(src, k, y, z, slot_of(0), xB));
+        const uint32_t lo = __builtin_bit_cast(uint16_t, ld_slot<kSlots<S>, false>(src, k, y, z, Q, xB));
+        return __uint_as_float((hi << 16) | lo);
     } else if constexpr (I == 0) {
         const auto r = row_rsrc(src + (size_t)row_of(k, y, z) * (kSlots<S> * (uint32_t)k.rs),
                                 kSlots<S> * (uint32_t)k.rs);
@@ -545,8 +558,8 @@ __device__ __forceinline__ float pull_dev(const typename S::T* __restrict__ src,
         return __uint_as_float((hi << 16) | lo);
     } else {
         int m;
-        const uint4 q = pull_rec<BC, I>(k.Qrec, k, y, z, xo, m);
-        return S::dec(pull_raw<BC, S, I>(src, k, y, z, xo)) + ref_part<I>(dec_ref<S>(mirror_ref(q, m)));
+        const uint4 q = pull_rec<BC, I, ROW>(k.Qrec, k, y, z, xo, m);
+        return S::dec(pull_raw<BC, S, I, ROW>(src, k, y, z, xo)) + ref_part<I>(dec_ref<S>(mirror_ref(q, m)));
     }
 }
 
@@ -572,18 +585,18 @@ __device__ __forceinline__ void colours_of(const KP& k, float d, const float4& r
     fb = bl ? fk : fo;
 }
 
-template <int BC, class S, bool WANT_F, int I = 0>
+template <int BC, class S, bool WANT_F, bool ROW = true, int I = 0>
 __device__ __forceinline__ void pull_dirs(const typename S::T* __restrict__ src, const KP& k, int x, int y, int z,
                                           const XOff& xo, float* d, float* fr, float* fb)
 {
     if constexpr (I < Q) {
-        d[I] = pull_dev<BC, S, I>(src, k, x, y, z, xo);
+        d[I] = pull_dev<BC, S, I, ROW>(src, k, x, y, z, xo);
         if constexpr (WANT_F) {
             int m;
-            const float4 r = pull_rec<BC, I>(k.R, k, y, z, xo, m);
+            const float4 r = pull_rec<BC, I, ROW>(k.R, k, y, z, xo, m);
             colours_of<I>(k, d[I], mirror_rec(r, m), fr[I], fb[I]);
         }
-        pull_dirs<BC, S, WANT_F, I + 1>(src, k, x, y, z, xo, d, fr, fb);
+        pull_dirs<BC, S, WANT_F, ROW, I + 1>(src, k, x, y, z, xo, d, fr, fb);
     }
 }
 
@@ -612,9 +625,8 @@ __device__ __forceinline__ void general_dirs(const typename S::T* __restrict__ s
     }
 }
 
-// the 27 pre-collision deviations (and colour populations) of a node; y and z
-// uniform over the wavefront
-template <int BC, class S, bool WANT_F>
+// the 27 pre-collision deviations (and colour populations) of a node
+template <int BC, class S, bool WANT_F, bool ROW = true>
 __device__ __forceinline__ void pull_all(const typename S::T* __restrict__ src, const KP& k, int x, int y, int z,
                                          float* d, float* fr, float* fb)
 {
@@ -622,7 +634,7 @@ __device__ __forceinline__ void pull_all(const typename S::T* __restrict__ src, 
         const uint32_t pn = pidx(k, x, y, z);
         general_dirs<S, WANT_F>(src, k, pn, WANT_F ? blue_kept(ldp(k.R, pn).x) : 0u, d, fr, fb);
     } else {
-        pull_dirs<BC, S, WANT_F>(src, k, x, y, z, x_offsets<BC, typename S::T>(k, x), d, fr, fb);
+        pull_dirs<BC, S, WANT_F, ROW>(src, k, x, y, z, x_offsets<BC, typename S::T>(k, x), d, fr, fb);
     }
 }
 
@@ -630,15 +642,15 @@ __device__ __forceinline__ void pull_all(const typename S::T* __restrict__ src, 
 // condition f(N) = [f_prev(N) + lam f(N - 1)] / (1 + lam), lam = max(0, u_z(N - 1))
 // evaluated on the freshly streamed populations of the node below; hprev holds
 // the outlet plane of the previous step (d, then f^r); blue is formed as f - f^r.
-template <class S>
+template <class S, bool ROW = true>
 __device__ void outlet_state(const typename S::T* __restrict__ src, const KP& k, const float* __restrict__ hprev,
                              const Node& nd, float* d, float* fr, float* fb)
 {
     if (k.unshifted) {
-        pull_all<LBM_BC_JET, S, true>(src, k, nd.x, nd.y, nd.z, d, fr, fb);
+        pull_all<LBM_BC_JET, S, true, ROW>(src, k, nd.x, nd.y, nd.z, d, fr, fb);
         return;
     }
-    pull_all<LBM_BC_JET, S, true>(src, k, nd.x, nd.y, nd.z - 1, d, fr, fb);
+    pull_all<LBM_BC_JET, S, true, ROW>(src, k, nd.x, nd.y, nd.z - 1, d, fr, fb);
     float m0 = 0.f, jz = 0.f;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -690,12 +702,17 @@ constexpr int BLOCK = 256;
 // times per node (the recolouring float4 R of the density pass, the (phi, rho)
 // fields of the gradient) once into LDS: a window of the tile plus a one-node
 // rim in x and y, over planes z - 1, z, z + 1, loaded row by row.
-constexpr int STX = 128, STY = BLOCK / STX;
 // Tiles of the step kernels: CX x CY nodes in the fused kernel, DX x DY in the
 // density pass.
 template <int X, int D>
 struct StepTiles {
     static constexpr int CX = X, CY = BLOCK / X, DX = X, DY = D / X;
+    static constexpr bool kFlat = false;
+};
+// no tiles: blocks of 256 consecutive nodes of a plane, neighbours through the caches
+struct NodeBlocks {
+    static constexpr int CX = BLOCK, CY = 1, DX = BLOCK, DY = 1;
+    static constexpr bool kFlat = true;
 };
 using WideTiles = StepTiles<128, 512>;
 using NarrowTiles = StepTiles<64, 256>;
@@ -1573,59 +1590,87 @@ __global__ __launch_bounds__(BLOCK) void k_set_state(typename S::T* __restrict__
     }
 }
 
-// Full pre-collision state (deviations and both colours) of the nodes of a tile;
-// the records R of the neighbours come from an LDS window (stage_records first).
-template <int BC>
-__device__ __forceinline__ void stage_records(const KP& k, const Tile& t, float4* __restrict__ win)
+// The kernels that read a state node by node (macroscopic fields, get_state, the first
+// pass of the diagnostics) take the tiles of the fused collision, the records R of the
+// neighbours from an LDS window, or NodeBlocks, where every lane has a row of its own
+// and the records come through the caches, for rows that leave too many lanes of a tile
+// idle (see read_form).
+template <class TL>
+constexpr int kRecWin = TL::kFlat ? 1 : TileShape<TL::CX, TL::CY>::W;
+
+// the tile of this block and its window, or this thread's node
+template <int BC, class TL>
+__device__ __forceinline__ Tile state_tile(const KP& k, float4* __restrict__ win)
 {
-    if (!k.unshifted)
-        stage_window<STX, STY>(k, t, [&](int x, int y, int z) { return rec_at<BC, true>(k, k.R, x, y, z); },
-                                     [&](int x, int y, int z) { return rec_at<BC>(k, k.R, x, y, z); },
-                               [&](int w, const float4& v) { win[w] = v; });
-    __syncthreads();
+    if constexpr (TL::kFlat) {
+        Tile t{};
+        t.nd = this_node(k);
+        t.z = t.nd.z;
+        return t;
+    } else {
+        const Tile t = this_tile<TL::CX, TL::CY>(k);
+        if (!k.unshifted)
+            stage_window<TL::CX, TL::CY>(k, t, [&](int x, int y, int z) { return rec_at<BC, true>(k, k.R, x, y, z); },
+                                         [&](int x, int y, int z) { return rec_at<BC>(k, k.R, x, y, z); },
+                                   [&](int w, const float4& v) { win[w] = v; });
+        __syncthreads();
+        return t;
+    }
 }
 
-template <int BC, class S, int I = 0>
+// record R of the source of direction I
+template <int BC, class TL, int I>
+__device__ __forceinline__ float4 source_rec(const KP& k, const Tile& t, const XOff& xo, const float4* __restrict__ win)
+{
+    if constexpr (TL::kFlat) {
+        int m;
+        const float4 r = pull_rec<BC, I, false>(k.R, k, t.nd.y, t.nd.z, xo, m);
+        return BC == LBM_BC_JET ? mirror_rec(r, m) : r;
+    } else {
+        return win[wslot<TL::CX, TL::CY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
+    }
+}
+
+template <int BC, class S, class TL, int I = 0>
 __device__ __forceinline__ void state_dirs(const typename S::T* __restrict__ src, const KP& k, const Tile& t,
                                            const XOff& xo, const float4* __restrict__ win, float* d, float* fr,
                                            float* fb)
 {
     if constexpr (I < Q) {
-        d[I] = pull_dev<BC, S, I>(src, k, t.nd.x, t.nd.y, t.nd.z, xo);
-        colours_of<I>(k, d[I], win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], fr[I], fb[I]);
-        state_dirs<BC, S, I + 1>(src, k, t, xo, win, d, fr, fb);
+        d[I] = pull_dev<BC, S, I, !TL::kFlat>(src, k, t.nd.x, t.nd.y, t.nd.z, xo);
+        colours_of<I>(k, d[I], source_rec<BC, TL, I>(k, t, xo, win), fr[I], fb[I]);
+        state_dirs<BC, S, TL, I + 1>(src, k, t, xo, win, d, fr, fb);
     }
 }
 
-template <int BC, class S>
+template <int BC, class S, class TL>
 __device__ __forceinline__ void read_state(const typename S::T* __restrict__ src, const KP& k,
                                            const float* __restrict__ hprev, const Tile& t,
                                            const float4* __restrict__ win, float* d, float* fr, float* fb)
 {
     const Node& nd = t.nd;
     if (BC == LBM_BC_JET && nd.z == k.nz - 1)
-        outlet_state<S>(src, k, hprev, nd, d, fr, fb);
+        outlet_state<S, !TL::kFlat>(src, k, hprev, nd, d, fr, fb);
     else if (k.unshifted)
-        pull_all<BC, S, true>(src, k, nd.x, nd.y, nd.z, d, fr, fb);
+        pull_all<BC, S, true, !TL::kFlat>(src, k, nd.x, nd.y, nd.z, d, fr, fb);
     else
-        state_dirs<BC, S>(src, k, t, x_offsets<BC, typename S::T>(k, nd.x), win, d, fr, fb);
+        state_dirs<BC, S, TL>(src, k, t, x_offsets<BC, typename S::T>(k, nd.x), win, d, fr, fb);
 }
 
 // current state as (fr, fb) FP32 in node order
-template <int BC, class S>
+template <int BC, class S, class TL>
 __global__ __launch_bounds__(BLOCK) void k_get_state(const typename S::T* __restrict__ src,
                                                       const float* __restrict__ hprev, KP k, float* __restrict__ st,
                                                       double rho_b0)
 {
-    __shared__ float4 win[TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
+    __shared__ float4 win[kRecWin<TL>];
+    const Tile t = state_tile<BC, TL>(k, win);
     const Node& nd = t.nd;
-    stage_records<BC>(k, t, win);
     if (!nd.valid) return;
     const size_t N = k.N;
     const uint32_t u_idx = (uint32_t)nd.z * k.plane + nd.q;
     float d[Q], fr[Q], fb[Q];
-    read_state<BC, S>(src, k, hprev, t, win, d, fr, fb);
+    read_state<BC, S, TL>(src, k, hprev, t, win, d, fr, fb);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         st[(size_t)i * N + u_idx] = fr[i];
@@ -1636,12 +1681,12 @@ __global__ __launch_bounds__(BLOCK) void k_get_state(const typename S::T* __rest
 // FP64 sums over the directions of a shifted state: the mass m0 = rho - rho_b0, the
 // momentum and the kept colour's mass mk; marks has bit 0 set where every source
 // kept blue, bit 1 where any did.
-template <int I = 0>
-__device__ __forceinline__ void mass_dirs(const KP& k, const Tile& t, const float4* __restrict__ win, const float* d,
-                                          double& m0, double& mk, double (&j)[3], uint32_t& marks)
+template <int BC, class TL, int I = 0>
+__device__ __forceinline__ void mass_dirs(const KP& k, const Tile& t, const XOff& xo, const float4* __restrict__ win,
+                                          const float* d, double& m0, double& mk, double (&j)[3], uint32_t& marks)
 {
     if constexpr (I < Q) {
-        const float4 r = win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
+        const float4 r = source_rec<BC, TL, I>(k, t, xo, win);
         const uint32_t bl = blue_kept(r.x);
         const float f = d[I] + wgt(I) * k.rho_b0;
         const float vt = I == 0 ? 0.f : (wgt(I) * inv_len(I)) * cdot(I, r.y, r.z, r.w);
@@ -1651,22 +1696,22 @@ __device__ __forceinline__ void mass_dirs(const KP& k, const Tile& t, const floa
         if (kCX[I]) j[0] += kCX[I] * (double)d[I];
         if (kCY[I]) j[1] += kCY[I] * (double)d[I];
         if (kCZ[I]) j[2] += kCZ[I] * (double)d[I];
-        if (I % 3 == 2) __builtin_amdgcn_sched_barrier(0);
-        mass_dirs<I + 1>(k, t, win, d, m0, mk, j, marks);
+        if (!TL::kFlat && I % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+        mass_dirs<BC, TL, I + 1>(k, t, xo, win, d, m0, mk, j, marks);
     }
 }
 
-template <int I = 0>
-__device__ __forceinline__ void mixed_masses(const KP& k, const Tile& t, const float4* __restrict__ win, const float* d,
-                                             double& rr, double& rb)
+template <int BC, class TL, int I = 0>
+__device__ __forceinline__ void mixed_masses(const KP& k, const Tile& t, const XOff& xo,
+                                             const float4* __restrict__ win, const float* d, double& rr, double& rb)
 {
     if constexpr (I < Q) {
         float fr, fb;
-        colours_of<I>(k, d[I], win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], fr, fb);
+        colours_of<I>(k, d[I], source_rec<BC, TL, I>(k, t, xo, win), fr, fb);
         rr += (double)fr;
         rb += (double)fb;
         if (I % 3 == 2) __builtin_amdgcn_sched_barrier(0);
-        mixed_masses<I + 1>(k, t, win, d, rr, rb);
+        mixed_masses<BC, TL, I + 1>(k, t, xo, win, d, rr, rb);
     }
 }
 
@@ -1674,7 +1719,7 @@ __device__ __forceinline__ void mixed_masses(const KP& k, const Tile& t, const f
 // sources kept the same colour, which is everywhere but next to phi = 0, its mass is
 // the sum of the kept values and the other colour the rest; else both colours are
 // rebuilt direction by direction.
-template <int BC, class S>
+template <int BC, class S, class TL>
 __device__ __forceinline__ void node_masses(const typename S::T* __restrict__ src, const KP& k,
                                             const float* __restrict__ hprev, const Tile& t,
                                             const float4* __restrict__ win, double& m0, double& rr, double& rb,
@@ -1682,23 +1727,24 @@ __device__ __forceinline__ void node_masses(const typename S::T* __restrict__ sr
 {
     m0 = rr = rb = j[0] = j[1] = j[2] = 0.0;
     const Node& nd = t.nd;
-    if (!k.unshifted && !(BC == LBM_BC_JET && nd.z == k.nz - 1)) {
+    if (!TL::kFlat && !k.unshifted && !(BC == LBM_BC_JET && nd.z == k.nz - 1)) {
         float d[Q], unused[Q];
         double mk = 0.0;
         uint32_t marks = 1u;
-        pull_dirs<BC, S, false>(src, k, nd.x, nd.y, nd.z, x_offsets<BC, typename S::T>(k, nd.x), d, unused, unused);
-        mass_dirs(k, t, win, d, m0, mk, j, marks);
+        const XOff xo = x_offsets<BC, typename S::T>(k, nd.x);
+        pull_dirs<BC, S, false, !TL::kFlat>(src, k, nd.x, nd.y, nd.z, xo, d, unused, unused);
+        mass_dirs<BC, TL>(k, t, xo, win, d, m0, mk, j, marks);
         const double other = (double)k.rho_b0 + m0 - mk;
         rr = marks ? other : mk;
         rb = marks ? mk : other;
         if (marks == 2u) {  // mixed
             rr = rb = 0.0;
-            mixed_masses(k, t, win, d, rr, rb);
+            mixed_masses<BC, TL>(k, t, xo, win, d, rr, rb);
         }
         return;
     }
     float d[Q], fr[Q], fb[Q];
-    read_state<BC, S>(src, k, hprev, t, win, d, fr, fb);
+    read_state<BC, S, TL>(src, k, hprev, t, win, d, fr, fb);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         m0 += (double)d[i];
@@ -1711,20 +1757,19 @@ __device__ __forceinline__ void node_masses(const typename S::T* __restrict__ sr
 }
 
 // macroscopic fields (node order) and FP64 audit partial sums (one slot per block)
-template <int BC, class S>
+template <int BC, class S, class TL>
 __global__ __launch_bounds__(BLOCK) void k_macro(const typename S::T* __restrict__ src,
                                                   const float* __restrict__ hprev, KP k, float* __restrict__ o_rr,
                                                   float* __restrict__ o_rb, float* __restrict__ o_u,
                                                   float* __restrict__ o_phi, double* __restrict__ partials)
 {
-    __shared__ float4 win[TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
+    __shared__ float4 win[kRecWin<TL>];
+    const Tile t = state_tile<BC, TL>(k, win);
     const Node& nd = t.nd;
-    stage_records<BC>(k, t, win);
     double acc[5] = {0, 0, 0, 0, 0};
     if (nd.valid) {
         double m0, rr, rb, j[3];
-        node_masses<BC, S>(src, k, hprev, t, win, m0, rr, rb, j);
+        node_masses<BC, S, TL>(src, k, hprev, t, win, m0, rr, rb, j);
         const double rho = (double)k.rho_b0 + m0;
         const double px = j[0] + 0.5 * m0 * k.gx, py = j[1] + 0.5 * m0 * k.gy, pz = j[2] + 0.5 * m0 * k.gz;
         const size_t n = (size_t)nd.z * k.plane + nd.q;

@@ -135,29 +135,28 @@ __device__ __forceinline__ double inlet_feq19(const KP& k, int i, int xg, int yg
     return (double)k.rho_r0 * (ph + w19(i) * poly);
 }
 
-// Deviation of direction I streamed into node (x, y, z) of the shifted form, row
-// uniform (offsets xo of x).  Not for the jet's outlet plane, which the convective
-// rule fills.
-template <int BC, int I>
+// Deviation of direction I streamed into node (x, y, z) of the shifted form (offsets
+// xo of x; ROW: the row is uniform over the wavefront).  Not for the jet's outlet
+// plane, which the convective rule fills.
+template <int BC, int I, bool ROW = true>
 __device__ __forceinline__ float pull19(const float* __restrict__ pop, const KP& k, int y, int z, const XOff& xo)
 {
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
     // first of the three slots that the offsets count from
     constexpr int base = slot19(I) - cx - 1, mbase = slot19(mirror_dir(I, 2)) - cx - 1;
+    int ys, zs;
     bool my;
-    const uint32_t row = group_row<BC, cy, cz>(k, y, z, my);
-    const uint32_t rs = (uint32_t)k.rs;
-    const auto r = row_rsrc(pop + (size_t)row * (Q19 * rs) + (uint32_t)(my ? mbase : base) * rs, 3u * rs);
-    return ld_row<float>(r, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o), 0u);
+    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
+    return ld_slot<Q19, ROW>(pop, k, ys, zs, my ? mbase : base, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
 }
 
-template <int BC, int I = 0>
+template <int BC, bool ROW = true, int I = 0>
 __device__ __forceinline__ void pull_all19(const float* __restrict__ pop, const KP& k, int y, int z, const XOff& xo,
                                            float* d)
 {
     if constexpr (I < Q19) {
-        d[I] = pull19<BC, I>(pop, k, y, z, xo);
-        pull_all19<BC, I + 1>(pop, k, y, z, xo, d);
+        d[I] = pull19<BC, I, ROW>(pop, k, y, z, xo);
+        pull_all19<BC, ROW, I + 1>(pop, k, y, z, xo, d);
     }
 }
 
@@ -176,22 +175,23 @@ __device__ __forceinline__ void general_pop(const float* __restrict__ pop, const
 // f(N, t) = [f(N, t - 1) + lam f(N - 1, t)] / (1 + lam), lam = max(0, u_z(N - 1, t))
 // with u_z of the freshly streamed plane below (half-force term included);
 // hist holds f(N, t - 1) as (d, fr) planes.  Both colours.
-template <int I = 0>
+template <bool ROW, int I = 0>
 __device__ __forceinline__ void below_dirs(const float* __restrict__ pop, const KP& k, const Node& nd, const XOff& xo,
                                            double (&d)[Q19], double (&fr)[Q19])
 {
     if constexpr (I < Q19) {
         int m;
-        const float4 r = pull_rec<LBM_BC_JET, I>(records(pop, k), k, nd.y, k.nz - 2, xo, m);
-        d[I] = (double)pull19<LBM_BC_JET, I>(pop, k, nd.y, k.nz - 2, xo);
+        const float4 r = pull_rec<LBM_BC_JET, I, ROW>(records(pop, k), k, nd.y, k.nz - 2, xo, m);
+        d[I] = (double)pull19<LBM_BC_JET, I, ROW>(pop, k, nd.y, k.nz - 2, xo);
         fr[I] = red_part(mirror_rec(r, m), I, d[I] + w19(I) * k.rho_b0);
-        below_dirs<I + 1>(pop, k, nd, xo, d, fr);
+        below_dirs<ROW, I + 1>(pop, k, nd, xo, d, fr);
     }
 }
+template <bool ROW>
 __device__ __forceinline__ void outlet_rule(const float* __restrict__ pop, const float* __restrict__ hist,
                                             const KP& k, const Node& nd, double (&d)[Q19], double (&fr)[Q19])
 {
-    below_dirs(pop, k, nd, x_offsets<LBM_BC_JET, float>(k, nd.x), d, fr);
+    below_dirs<ROW>(pop, k, nd, x_offsets<LBM_BC_JET, float>(k, nd.x), d, fr);
     double m = 0.0, jz = 0.0;
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
@@ -222,20 +222,53 @@ __device__ __forceinline__ void stage_records19(const float* __restrict__ pop, c
 // node order index
 __device__ __forceinline__ uint32_t order_of(const KP& k, const Node& nd) { return (uint32_t)nd.z * k.plane + nd.q; }
 
-// The state at a node of the tile: the populations after streaming, (d_i, fr_i), of
-// either form; the jet's outlet plane from the general form, or by the rule.  The
-// records are in the window (shifted form).
-template <int BC, int I = 0>
-__device__ __forceinline__ void window_dirs(const float* __restrict__ pop, const KP& k, const Tile& t, const XOff& xo,
-                                            const float4* __restrict__ win, double (&d)[Q19], double (&fr)[Q19])
+// record of the source of direction I: from the window, or (NodeBlocks) through the caches
+template <int BC, class TL, int TX, int TY, int I>
+__device__ __forceinline__ float4 source_rec19(const float* __restrict__ pop, const KP& k, const Tile& t,
+                                               const XOff& xo, const float4* __restrict__ win)
 {
-    if constexpr (I < Q19) {
-        d[I] = (double)pull19<BC, I>(pop, k, t.nd.y, t.nd.z, xo);
-        fr[I] = red_part(win[wslot<STX, STY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], I, d[I] + w19(I) * k.rho_b0);
-        window_dirs<BC, I + 1>(pop, k, t, xo, win, d, fr);
+    if constexpr (TL::kFlat) {
+        int m;
+        const float4 r = pull_rec<BC, I, false>(records(pop, k), k, t.nd.y, t.nd.z, xo, m);
+        return BC == LBM_BC_JET ? mirror_rec(r, m) : r;
+    } else {
+        return win[wslot<TX, TY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
     }
 }
-template <bool GEN, int BC>
+
+// the tile of this block with the records of its nodes and rim in the window
+// (shifted form), or (NodeBlocks) this thread's node
+template <bool GEN, int BC, class TL>
+__device__ __forceinline__ Tile state_tile19(const float* __restrict__ pop, const KP& k, float4* __restrict__ win)
+{
+    if constexpr (TL::kFlat) {
+        Tile t{};
+        t.nd = this_node(k);
+        t.z = t.nd.z;
+        return t;
+    } else {
+        const Tile t = this_tile<TL::CX, TL::CY>(k);
+        if (!GEN) {
+            stage_records19<BC, TL::CX, TL::CY>(pop, k, t, win);
+            __syncthreads();
+        }
+        return t;
+    }
+}
+
+// The state at a node: the populations after streaming, (d_i, fr_i), of either form;
+// the jet's outlet plane from the general form, or by the rule.
+template <int BC, class TL, int I = 0>
+__device__ __forceinline__ void state_dirs19(const float* __restrict__ pop, const KP& k, const Tile& t, const XOff& xo,
+                                             const float4* __restrict__ win, double (&d)[Q19], double (&fr)[Q19])
+{
+    if constexpr (I < Q19) {
+        d[I] = (double)pull19<BC, I, !TL::kFlat>(pop, k, t.nd.y, t.nd.z, xo);
+        fr[I] = red_part(source_rec19<BC, TL, TL::CX, TL::CY, I>(pop, k, t, xo, win), I, d[I] + w19(I) * k.rho_b0);
+        state_dirs19<BC, TL, I + 1>(pop, k, t, xo, win, d, fr);
+    }
+}
+template <bool GEN, int BC, class TL>
 __device__ __forceinline__ void node_state(const float* __restrict__ pop, const float* __restrict__ hist, const KP& k,
                                            const Tile& t, const float4* __restrict__ win, double (&d)[Q19],
                                            double (&fr)[Q19])
@@ -244,9 +277,9 @@ __device__ __forceinline__ void node_state(const float* __restrict__ pop, const 
 #pragma unroll
         for (int i = 0; i < Q19; ++i) general_pop(pop, k, order_of(k, t.nd), i, d[i], fr[i]);
     } else if (BC == LBM_BC_JET && t.nd.z == k.nz - 1) {
-        outlet_rule(pop, hist, k, t.nd, d, fr);
+        outlet_rule<!TL::kFlat>(pop, hist, k, t.nd, d, fr);
     } else {
-        window_dirs<BC>(pop, k, t, x_offsets<BC, float>(k, t.nd.x), win, d, fr);
+        state_dirs19<BC, TL>(pop, k, t, x_offsets<BC, float>(k, t.nd.x), win, d, fr);
     }
 }
 
@@ -262,17 +295,18 @@ __device__ __forceinline__ void store_fields(float2* __restrict__ F, const KP& k
     stp(F + k.N, n, make_float2((float)rr, (float)rb));
 }
 
-template <int BC, int TX, int TY, int I = 0>
-__device__ __forceinline__ void density_dirs(const float* d, const KP& k, const Tile& t, const float4* __restrict__ win,
-                                             double& rr, double& rb, double& m)
+template <int BC, class TL, int I = 0>
+__device__ __forceinline__ void density_dirs(const float* __restrict__ pop, const float* d, const KP& k, const Tile& t,
+                                             const XOff& xo, const float4* __restrict__ win, double& rr, double& rb,
+                                             double& m)
 {
     if constexpr (I < Q19) {
         const double f = (double)d[I] + w19(I) * k.rho_b0;
-        const double fr = red_part(win[wslot<TX, TY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])], I, f);
+        const double fr = red_part(source_rec19<BC, TL, TL::DX, TL::DY, I>(pop, k, t, xo, win), I, f);
         m += (double)d[I];
         rr += fr;
         rb += f - fr;
-        density_dirs<BC, TX, TY, I + 1>(d, k, t, win, rr, rb, m);
+        density_dirs<BC, TL, I + 1>(pop, d, k, t, xo, win, rr, rb, m);
     }
 }
 
@@ -283,13 +317,18 @@ __global__ __launch_bounds__(TL::DX* TL::DY) void k19_density(const float* __res
                                                               KP k)
 {
     constexpr int TX = TL::DX, TY = TL::DY;
-    __shared__ float4 win[GEN ? 1 : TileShape<TX, TY>::W];
-    const Tile t = this_tile<TX, TY>(k);
-    double rr = 0.0, rb = 0.0, m = 0.0;
-    if (!GEN) {
-        stage_records19<BC, TX, TY>(pop, k, t, win);
-        __syncthreads();
+    __shared__ float4 win[GEN || TL::kFlat ? 1 : TileShape<TX, TY>::W];
+    Tile t{};
+    if constexpr (TL::kFlat) {
+        t.nd = this_node(k);
+    } else {
+        t = this_tile<TX, TY>(k);
+        if (!GEN) {
+            stage_records19<BC, TX, TY>(pop, k, t, win);
+            __syncthreads();
+        }
     }
+    double rr = 0.0, rb = 0.0, m = 0.0;
     if (!t.nd.valid) return;
     if (GEN) {
 #pragma unroll
@@ -302,8 +341,9 @@ __global__ __launch_bounds__(TL::DX* TL::DY) void k19_density(const float* __res
         }
     } else {
         float d[Q19];
-        pull_all19<BC>(pop, k, t.nd.y, t.nd.z, x_offsets<BC, float>(k, t.nd.x), d);
-        density_dirs<BC, TX, TY>(d, k, t, win, rr, rb, m);
+        const XOff xo = x_offsets<BC, float>(k, t.nd.x);
+        pull_all19<BC, !TL::kFlat>(pop, k, t.nd.y, t.nd.z, xo, d);
+        density_dirs<BC, TL>(pop, d, k, t, xo, win, rr, rb, m);
     }
     store_fields(F, k, order_of(k, t.nd), rr, rb, m);
 }
@@ -330,7 +370,7 @@ __global__ __launch_bounds__(OBLOCK) void k19_outlet(const float* __restrict__ p
 #pragma unroll
         for (int i = 0; i < Q19; ++i) general_pop(pop, k, order_of(k, nd), i, d[i], fr[i]);
     } else {
-        outlet_rule(pop, hprev, k, nd, d, fr);
+        outlet_rule<true>(pop, hprev, k, nd, d, fr);
     }
     double rr = 0.0, rb = 0.0, m = 0.0;
     const size_t P = k.plane;
@@ -372,19 +412,20 @@ __device__ __forceinline__ float2 field_at(const float2* __restrict__ F, const K
 // isotropic gradients of phi and rho, 3 sum_i w_i chi(x + c_i) c_i, summed
 // over the opposite pairs (i, i + 1) as differences: exactly zero on a
 // uniform field, which keeps the recolouring off there
-template <int TX, int TY, int I = 1>
-__device__ __forceinline__ void gradients(const float2* __restrict__ win, const Tile& t, double& gpx, double& gpy,
-                                          double& gpz, double& grx, double& gry, double& grz)
+// at(dx, dy, dz): (phi, rho - rho_b0) of the neighbour
+template <int I = 1, class A>
+__device__ __forceinline__ void gradients(const A& at, double& gpx, double& gpy, double& gpz, double& grx, double& gry,
+                                          double& grz)
 {
     if constexpr (I < Q19) {
-        const float2 qp = win[wslot<TX, TY>(t.lx, t.ly, kCX[I], kCY[I], kCZ[I])];
-        const float2 qm = win[wslot<TX, TY>(t.lx, t.ly, -kCX[I], -kCY[I], -kCZ[I])];
+        const float2 qp = at(kCX[I], kCY[I], kCZ[I]);
+        const float2 qm = at(-kCX[I], -kCY[I], -kCZ[I]);
         const double tp = 3.0 * w19(I) * ((double)qp.x - (double)qm.x);
         const double tr = 3.0 * w19(I) * ((double)qp.y - (double)qm.y);
         if (kCX[I]) { gpx += kCX[I] * tp; grx += kCX[I] * tr; }
         if (kCY[I]) { gpy += kCY[I] * tp; gry += kCY[I] * tr; }
         if (kCZ[I]) { gpz += kCZ[I] * tp; grz += kCZ[I] * tr; }
-        gradients<TX, TY, I + 2>(win, t, gpx, gpy, gpz, grx, gry, grz);
+        gradients<I + 2>(at, gpx, gpy, gpz, grx, gry, grz);
     }
 }
 
@@ -416,13 +457,19 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
                                                      KP k, Consts c)
 {
     constexpr int TX = TL::CX, TY = TL::CY;
-    __shared__ float2 win[TileShape<TX, TY>::W];
-    const Tile t = this_tile<TX, TY>(k);
+    constexpr bool FLAT = TL::kFlat;
+    __shared__ float2 win[FLAT ? 1 : TileShape<TX, TY>::W];
+    Tile t{};
+    if constexpr (FLAT) {
+        t.nd = this_node(k);
+    } else {
+        t = this_tile<TX, TY>(k);
+        stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return field_at<BC, true>(F, k, x, y, z); },
+                             [&](int x, int y, int z) { return field_at<BC>(F, k, x, y, z); },
+                             [&](int w, const float2& v) { win[w] = v; });
+        __syncthreads();
+    }
     const Node& nd = t.nd;
-    stage_window<TX, TY>(k, t, [&](int x, int y, int z) { return field_at<BC, true>(F, k, x, y, z); },
-                         [&](int x, int y, int z) { return field_at<BC>(F, k, x, y, z); },
-                         [&](int w, const float2& v) { win[w] = v; });
-    __syncthreads();
     if (!nd.valid) return;
     const size_t N = k.N;
     float d[Q19];
@@ -433,12 +480,18 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
 #pragma unroll
         for (int i = 0; i < Q19; ++i) d[i] = src[(size_t)i * N + order_of(k, nd)];
     } else {
-        pull_all19<BC>(src, k, nd.y, nd.z, x_offsets<BC, float>(k, nd.x), d);
+        pull_all19<BC, !FLAT>(src, k, nd.y, nd.z, x_offsets<BC, float>(k, nd.x), d);
     }
-    const float2 P = win[wslot<TX, TY>(t.lx, t.ly, 0, 0, 0)], Q = ldp(F + k.N, order_of(k, nd));
+    const auto at = [&](int dx, int dy, int dz) -> float2 {
+        if constexpr (FLAT)
+            return field_at<BC>(F, k, nd.x + dx, nd.y + dy, nd.z + dz);
+        else
+            return win[wslot<TX, TY>(t.lx, t.ly, dx, dy, dz)];
+    };
+    const float2 P = at(0, 0, 0), Q = ldp(F + k.N, order_of(k, nd));
     const double phi = P.x, m = P.y, rr = Q.x, rb = Q.y;
     double gpx = 0, gpy = 0, gpz = 0, grx = 0, gry = 0, grz = 0;
-    gradients<TX, TY>(win, t, gpx, gpy, gpz, grx, gry, grz);
+    gradients(at, gpx, gpy, gpz, grx, gry, grz);
     // interpolated properties, body force, velocity (Eqs. bodyForceJet, Momentum)
     const double rho = c.rho_b0 + m;
     const double hp = 0.5 * (1.0 + phi);
@@ -501,13 +554,20 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
     const bool bottom = BC == LBM_BC_JET && nd.z == 0;
     const bool gcell = bottom && !inlet_inside(k, nd.x, nd.y);
     const uint32_t grow = BC == LBM_BC_JET ? row_of(k, nd.y, -1) : 0u;
-    const auto rd = row_rsrc(dst + (size_t)row * (uint32_t)(Q19 * k.rs), (uint32_t)(Q19 * k.rs));
-    const auto rg = row_rsrc(dst + (size_t)grow * (uint32_t)(Q19 * k.rs), (uint32_t)(Q19 * k.rs));
+    const auto put = [&](uint32_t r, int slot, float v) {
+        float* b = dst + (size_t)r * (uint32_t)(Q19 * k.rs);
+        if constexpr (!FLAT)
+            st_row<NT>(row_rsrc(b, (uint32_t)(Q19 * k.rs)), xB, (uint32_t)slot * rsB, v);
+        else if constexpr (NT)
+            __builtin_nontemporal_store(v, b + (uint32_t)slot * (uint32_t)k.rs + nd.x);
+        else
+            b[(uint32_t)slot * (uint32_t)k.rs + nd.x] = v;
+    };
     const auto store = [&](int i, double f) {
         const float v = (float)f;
-        st_row<NT>(rd, xB, (uint32_t)slot19(i) * rsB, v);
+        put(row, slot19(i), v);
         if (BC == LBM_BC_JET && kCZ[i] < 0 && bottom) {  // uniform: leaves downwards
-            if (gcell) st_row<NT>(rg, xB, (uint32_t)slot19(mirror_dir(i, 4)) * rsB, v);
+            if (gcell) put(grow, slot19(mirror_dir(i, 4)), v);
         }
     };
     // rest population
@@ -558,27 +618,28 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
     const float xm = rr <= rb ? (float)(rr * irc) : -(float)(rb * irc);
     const float4 rv = make_float4(xm, (float)(vs * gpx), (float)(vs * gpy), (float)(vs * gpz));
     float4* R = const_cast<float4*>(records(dst, k));
-    st_rec<NT>(R, k, row, nd.x, rv);
-    if (gcell) st_rec<NT>(R, k, grow, nd.x, mirror_rec(rv, 4));
+    if constexpr (FLAT) {
+        R[(size_t)row * (uint32_t)k.rs + nd.x] = rv;
+        if (gcell) R[(size_t)grow * (uint32_t)k.rs + nd.x] = mirror_rec(rv, 4);
+    } else {
+        st_rec<NT>(R, k, row, nd.x, rv);
+        if (gcell) st_rec<NT>(R, k, grow, nd.x, mirror_rec(rv, 4));
+    }
 }
 
 // Macroscopic fields (node order) and FP64 audit partial sums, one slot per block.
-template <bool GEN, int BC>
+template <bool GEN, int BC, class TL>
 __global__ __launch_bounds__(BLOCK) void k19_macro(const float* __restrict__ pop, const float* __restrict__ hist, KP k,
                                                    float* __restrict__ o_rr, float* __restrict__ o_rb,
                                                    float* __restrict__ o_u, float* __restrict__ o_phi,
                                                    double* __restrict__ partials)
 {
-    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
-    if (!GEN) {
-        stage_records19<BC, STX, STY>(pop, k, t, win);
-        __syncthreads();
-    }
+    __shared__ float4 win[GEN ? 1 : kRecWin<TL>];
+    const Tile t = state_tile19<GEN, BC, TL>(pop, k, win);
     double acc[5] = {0, 0, 0, 0, 0};
     if (t.nd.valid) {
         double d[Q19], fv[Q19];
-        node_state<GEN, BC>(pop, hist, k, t, win, d, fv);
+        node_state<GEN, BC, TL>(pop, hist, k, t, win, d, fv);
         double m0 = 0.0, rr = 0.0, rb = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
 #pragma unroll
         for (int i = 0; i < Q19; ++i) {
@@ -613,20 +674,16 @@ __global__ __launch_bounds__(BLOCK) void k19_macro(const float* __restrict__ pop
 }
 
 // the state fr[i N + n], fb[(19 + i) N + n] of either form
-template <bool GEN, int BC>
+template <bool GEN, int BC, class TL>
 __global__ __launch_bounds__(BLOCK) void k19_get_state(const float* __restrict__ pop, const float* __restrict__ hist,
                                                        KP k, float* __restrict__ st)
 {
-    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
-    if (!GEN) {
-        stage_records19<BC, STX, STY>(pop, k, t, win);
-        __syncthreads();
-    }
+    __shared__ float4 win[GEN ? 1 : kRecWin<TL>];
+    const Tile t = state_tile19<GEN, BC, TL>(pop, k, win);
     if (!t.nd.valid) return;
     const size_t N = k.N, n = order_of(k, t.nd);
     double d[Q19], fr[Q19];
-    node_state<GEN, BC>(pop, hist, k, t, win, d, fr);
+    node_state<GEN, BC, TL>(pop, hist, k, t, win, d, fr);
 #pragma unroll
     for (int i = 0; i < Q19; ++i) {
         st[(size_t)i * N + n] = (float)fr[i];
@@ -637,20 +694,16 @@ __global__ __launch_bounds__(BLOCK) void k19_get_state(const float* __restrict__
 // Jet diagnostics (Sec. IV C), first pass on D3Q19: the order parameter of the
 // current state binarised (phi as lbm_macroscopic returns it) and labels; the
 // union-find passes that follow are those of the D3Q27 path.
-template <bool GEN, int BC>
+template <bool GEN, int BC, class TL>
 __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__ pop, const float* __restrict__ hist,
                                                        KP k, DiagWork w)
 {
-    __shared__ float4 win[GEN ? 1 : TileShape<STX, STY>::W];
-    const Tile t = this_tile<STX, STY>(k);
-    if (!GEN) {
-        stage_records19<BC, STX, STY>(pop, k, t, win);
-        __syncthreads();
-    }
+    __shared__ float4 win[GEN ? 1 : kRecWin<TL>];
+    const Tile t = state_tile19<GEN, BC, TL>(pop, k, win);
     bool fg = false;
     if (t.nd.valid) {
         double d[Q19], fr[Q19];
-        node_state<GEN, BC>(pop, hist, k, t, win, d, fr);
+        node_state<GEN, BC, TL>(pop, hist, k, t, win, d, fr);
         double rr = 0.0, rb = 0.0;
 #pragma unroll
         for (int i = 0; i < Q19; ++i) {
@@ -661,7 +714,7 @@ __global__ __launch_bounds__(BLOCK) void k19_diag_init(const float* __restrict__
         fg = (float)((a - b) / (a + b)) > 0.f;
     }
     const unsigned long long m = __ballot(fg);
-    const int i = (int)order_of(k, t.nd), run = diag_run_label(m, i);
+    const int i = (int)order_of(k, t.nd), run = TL::kFlat ? i : diag_run_label(m, i);
     if (t.nd.valid) w.label[i] = fg ? run : -1;
     diag_tally(w, m, fg ? t.nd.z : -1);
 }

@@ -57,3 +57,14 @@ def test_every_tile_once(check):
     assert len(got) == len(TILES) * len(shapes)
     assert not any(w for (w,) in got), [(shapes[k // len(TILES)], TILES[k % len(TILES)])
                                         for k, (w,) in enumerate(got) if w]
+
+
+def test_audit_of_a_thin_lattice_is_small():
+    """One slot of five doubles per block of 256 nodes, not per two rows of a tile."""
+    from paper_1804_08923_amd.lbm import lbm_query_sizes, make_params
+    from paper_1804_08923_amd.workloads import Problem
+    for lattice in (27, 19):
+        prob = Problem(name="thin", nx=1, ny=4096, nz=4096, rho_r0=1.0, rho_b0=0.5, nu_r=0.02, nu_b=0.05, init="jet",
+                       lattice=lattice, alpha_b=8 / 27 if lattice == 27 else 1 / 3)
+        s = lbm_query_sizes(make_params(prob))
+        assert s.audit_bytes <= 40 * (s.n_nodes // 256 + 1)
