@@ -135,6 +135,26 @@ __device__ __forceinline__ double inlet_feq19(const KP& k, int i, int xg, int yg
     return (double)k.rho_r0 * (ph + w19(i) * poly);
 }
 
+// The inlet cells of the ghost plane keep their populations in FP64, as the inflow's
+// equilibrium is computed: the FP32 slot of a direction that enters the lattice holds
+// the rounded value, the slot of its mirror image, which nobody pulls there, the rest.
+// Density, fields and state add the rests to what they pull, add(i, rest) on the
+// bottom plane above the inlet (a pure red cell: the rest is red, too); the collision
+// works on FP32 deviations.  The density pass takes them before its pulls: after them
+// it holds 123 registers instead of 52, and the 128x128x512 jet takes 5 % longer.
+template <int BC, class A>
+__device__ __forceinline__ void inlet_rests(const float* __restrict__ pop, const KP& k, const Node& nd, const A& add)
+{
+    if (BC != LBM_BC_JET || nd.z != 0) return;
+#pragma unroll
+    for (int i = 1; i < Q19; ++i) {
+        if (kCZ[i] != 1) continue;
+        const int x = nd.x - kCX[i], y = nd.y - kCY[i];
+        if (inlet_inside(k, x, y))
+            add(i, (double)pop[((size_t)row_of(k, y, -1) * Q19 + slot19(mirror_dir(i, 4))) * (uint32_t)k.rs + x]);
+    }
+}
+
 // Deviation of direction I streamed into node (x, y, z) of the shifted form (offsets
 // xo of x; ROW: the row is uniform over the wavefront).  Not for the jet's outlet
 // plane, which the convective rule fills.
@@ -280,6 +300,10 @@ __device__ __forceinline__ void node_state(const float* __restrict__ pop, const 
         outlet_rule<!TL::kFlat>(pop, hist, k, t.nd, d, fr);
     } else {
         state_dirs19<BC, TL>(pop, k, t, x_offsets<BC, float>(k, t.nd.x), win, d, fr);
+        inlet_rests<BC>(pop, k, t.nd, [&](int i, double e) {
+            d[i] += e;
+            fr[i] += e;
+        });
     }
 }
 
@@ -340,6 +364,8 @@ __global__ __launch_bounds__(TL::DX* TL::DY) void k19_density(const float* __res
             rb += d + w19(i) * k.rho_b0 - fr;
         }
     } else {
+        inlet_rests<BC>(pop, k, t.nd, [&](int, double e) { m += e; });
+        rr = m;
         float d[Q19];
         const XOff xo = x_offsets<BC, float>(k, t.nd.x);
         pull_all19<BC, !TL::kFlat>(pop, k, t.nd.y, t.nd.z, xo, d);
@@ -352,8 +378,8 @@ __global__ __launch_bounds__(TL::DX* TL::DY) void k19_density(const float* __res
 // streaming (general form, or the convective rule from hprev) go to hcur as
 // (d, fr), where the collision and the next step's rule read them, and its
 // fields to F.  Also the inlet cells of the ghost plane of the state that the step
-// writes (the red equilibrium at this time level, rounded to FP32 like every stored
-// population, and a pure red record).
+// writes (the red equilibrium at this time level, see inlet_rests, and a pure red
+// record).
 template <bool GEN>
 __global__ __launch_bounds__(OBLOCK) void k19_outlet(const float* __restrict__ pop, float2* __restrict__ F,
                                                      const float* __restrict__ hprev, float* __restrict__ hcur,
@@ -386,10 +412,13 @@ __global__ __launch_bounds__(OBLOCK) void k19_outlet(const float* __restrict__ p
     if (inlet_inside(k, nd.x, nd.y)) {
         const uint32_t row = row_of(k, nd.y, -1), rs = (uint32_t)k.rs;
 #pragma unroll
-        for (int i = 1; i < Q19; ++i)
-            if (kCZ[i] == 1)
-                dst[(size_t)row * (Q19 * rs) + (uint32_t)slot19(i) * rs + nd.x] =
-                    (float)(inlet_feq19(k, i, nd.x, nd.y, k.t) - w19(i) * k.rho_b0);
+        for (int i = 1; i < Q19; ++i) {
+            if (kCZ[i] != 1) continue;
+            float* cell = dst + (size_t)row * (Q19 * rs) + nd.x;
+            const double v = inlet_feq19(k, i, nd.x, nd.y, k.t) - w19(i) * k.rho_b0;
+            cell[(uint32_t)slot19(i) * rs] = (float)v;
+            cell[(uint32_t)slot19(mirror_dir(i, 4)) * rs] = (float)(v - (double)(float)v);
+        }
         const_cast<float4*>(records(dst, k))[(size_t)row * rs + nd.x] = make_float4(-0.f, 0.f, 0.f, 0.f);
     }
 }
