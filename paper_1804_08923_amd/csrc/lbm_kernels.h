@@ -246,7 +246,7 @@ __device__ __forceinline__ void st_row(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
 }
 
 // 16-byte record (R, reference record) of node x of row `row` (uniform)
-template <bool NT, class T>
+template <class T>
 __device__ __forceinline__ void st_rec(T* __restrict__ base, const KP& k, uint32_t row, int x, T v)
 {
     static_assert(sizeof(T) == 16, "16-byte records");
@@ -1353,16 +1353,16 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
     // recolouring vector V = beta (rho_r rho_b / rho) kappa n (x_r x_b = xk (1 - xk))
     const float rec = k.beta * xk * (1.f - xk) * rhof * (float)kap * inv_gn;
     const float4 rv = make_float4(xk, rec * gpx, rec * gpy, rec * gpz);
-    st_rec<NT>(Rout, k, row, nd.x, rv);
-    if (gcell) st_rec<NT>(Rout, k, grow, nd.x, mirror_rec(rv, 4));
+    st_rec(Rout, k, row, nd.x, rv);
+    if (gcell) st_rec(Rout, k, grow, nd.x, mirror_rec(rv, 4));
     end_block(k);
     const float nub9 = 9.f * nubf;
     // referenced 16-bit storage: reference record of this node, rounded as stored
     float rt = 0.f, uxt = 0.f, uyt = 0.f, uzt = 0.f, et = 0.f;
     if constexpr (S::kEqRef) {
         const uint4 qr = enc_ref<S>(rhof, uxf, uyf, uzf, (float)E1);
-        st_rec<NT>(Qout, k, row, nd.x, qr);
-        if (gcell) st_rec<NT>(Qout, k, grow, nd.x, mirror_ref(qr, 4));
+        st_rec(Qout, k, row, nd.x, qr);
+        if (gcell) st_rec(Qout, k, grow, nd.x, mirror_ref(qr, 4));
         end_block(k);
         const RefRec r = dec_ref<S>(qr);
         rt = r.rho;
@@ -1444,11 +1444,13 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
 
 
 // ---------------------------------------------------------------- fused collide-recolour-stream
-// A state above this size (the 256 MB memory-side cache) is written with
-// non-temporal stores: nothing of it will be read from a cache in the next step, and
+// A state above this size (the 256 MB memory-side cache), populations and recolouring
+// records, has its populations written with non-temporal stores (the records with plain
+// ones: no difference): nothing of it will be read from a cache in the next step, and
 // the lines that the pulls share stay longer.  FP32 step 4.78 -> 4.68 ms (256x256x1024)
 // and 0.584 -> 0.561 ms (128x128x512); 100^3 nodes (124 MB) keep the plain stores,
-// 0.077 against 0.079 ms.
+// 0.077 against 0.079 ms.  The reference records are not counted: BF16_EQ, 150^3 nodes,
+// 359 us a step with plain stores, 366 without.
 constexpr uint64_t kCacheBytes = 256ull << 20;
 
 // waves per SIMD, measured on MI355X: four (at most 128 VGPRs) in FP32 and

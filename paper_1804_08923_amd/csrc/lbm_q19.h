@@ -651,8 +651,8 @@ __global__ __launch_bounds__(BLOCK) void k19_collide(const float* __restrict__ s
         R[(size_t)row * (uint32_t)k.rs + nd.x] = rv;
         if (gcell) R[(size_t)grow * (uint32_t)k.rs + nd.x] = mirror_rec(rv, 4);
     } else {
-        st_rec<NT>(R, k, row, nd.x, rv);
-        if (gcell) st_rec<NT>(R, k, grow, nd.x, mirror_rec(rv, 4));
+        st_rec(R, k, row, nd.x, rv);
+        if (gcell) st_rec(R, k, grow, nd.x, mirror_rec(rv, 4));
     }
 }
 

@@ -70,12 +70,12 @@ def test_q19_steps_from_a_random_state(torch, o19, shape):
     """Steps 1, 2 and 10 from a random state (tau != 1, gamma = 2, eta != 1,
     g != 0), every population of both colours against the oracle: step 1
     reads the general form set_state writes, the later steps the shifted form
-    the step writes.  300 x 2 planes are three 256-node blocks with a ragged
-    tail; 64 x 32 and 43 x 44 planes are 8 blocks (the second with a ragged
-    last one), which the kernels hand out in XCD bands, as 512 x 4 x 3 and
-    256 x 8 x 2; rows of 256 and 512 nodes are the bench's row shape
-    (256 x 1 x 1 with every neighbour row the same); one-node-thick axes make
-    a node its own periodic neighbour.  (The random state of 512 x 4 x 2 is
+    the step writes.  300 x 2 planes are three 128-node tiles a row, the last
+    ragged; 64 x 32 planes are 8 tiles, 43 x 44 planes 11 in bands over one row
+    of blocks, 256 x 8 x 2 8 tiles of the collision; rows of up to 35 nodes take
+    blocks of consecutive nodes; rows of 256 and 512 nodes are the bench's row
+    shape (256 x 1 x 1 with every neighbour row the same); one-node-thick axes
+    make a node its own periodic neighbour.  (The random state of 512 x 4 x 2 is
     ill-conditioned: there the FP32 rounding of the stored state alone, with
     exact arithmetic, moves u by 4.5e-5 in 10 steps.)"""
     prob = _prob(*shape)

@@ -1,8 +1,8 @@
 """The row layout of a running state against the FP64 oracle: row lengths around
 the 64-node segments and 128-node tiles of the step kernels (a tile whose right
 rim lies inside it, one node into the next tile, several tiles), strides that are
-longer than the row and strides that cannot be aligned, and one- and two-row
-lattices, on both boundary kinds.
+longer than the row and strides that cannot be aligned, on both boundary kinds
+(lattices of one and two rows: test_gpu_narrow_rows.py).
 
 Three steps from a random state: the first reads the state as it was set, the
 others read rows.  D3Q19 shares the layout and is held to its own oracle.
