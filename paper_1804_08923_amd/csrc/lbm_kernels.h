@@ -43,8 +43,9 @@
 //    z = nz - 1 (convective condition) and the inlet cells of the ghost plane
 //    have a small kernel of their own before them; the fused kernel writes the
 //    mirrored part of the ghost plane.
-//  * Launch geometry: see "stencil tiles"; every kernel gives a wavefront 64
-//    consecutive nodes of one row.
+//  * Launch geometry: see "stencil tiles"; a wavefront takes 64 consecutive nodes of
+//    one row, but for the kernels that take blocks of nodes on narrow rows
+//    (NodeBlocks) and the ones that only write the general form.
 //  * Collision: with s0 = s1 = 0 and s2b = s3..s6 = 1 (Sec. II) the GMRT
 //    collision (Eq. scoll) leaves every central moment at its equilibrium
 //    value plus half the forcing moment, except the five deviatoric second-
@@ -1023,7 +1024,7 @@ constexpr int kDensityWaves = (sizeof(typename S::T) == 2 && !S::kEqRef) ? 8 : 2
 // MOMS (the adjoint step from a snapshot): also the raw moments of the pulled
 // deviations into MOM.  A compile-time switch: the moment code would raise the step's
 // registers (FP32: to 90) and with them lower its waves.  330 us on the 128x128x512
-// jet, 268 B of traffic per node at 6.8 TB/s (518 us in the plane-major layout).
+// jet, 176 B of traffic per node at 4.5 TB/s (518 us in the plane-major layout).
 template <int BC, class S, class TL, bool MOMS = false>
 __global__ __launch_bounds__(TL::DX* TL::DY) __attribute__((amdgpu_waves_per_eu(kDensityWaves<S>, 8))) void k_density(
     const typename S::T* __restrict__ src, float2* __restrict__ PD, float* __restrict__ XR, KP k,
@@ -1070,11 +1071,13 @@ __global__ __launch_bounds__(TL::DX* TL::DY) __attribute__((amdgpu_waves_per_eu(
     if constexpr (MOMS) store_moments(MOM, k, (uint32_t)nd.z * k.plane + nd.q, (float)m0, d);
 }
 
-// Ends a basic block (the time level is never negative).  The compiler chooses
-// which product of a sum goes into a fused multiply-add by what else the block
-// holds; with its own ends the pairs of directions keep that choice, and with it
-// every last bit of the results, whatever is stored between them.  Scalar
-// branches, 10 per wave: no time that could be measured.
+// Ends a basic block (the time level is never negative).  With contraction on the
+// compiler chooses which product of a sum goes into a fused multiply-add, by what else
+// the block holds; in a block of their own the pairs of directions kept that choice
+// when the stores between them changed.  That is what one compiler does, not a property
+// of the code: another may round differently, which is no less exact, but in 16-bit
+// storage moves the fields of a run by up to 1e-3 of their size within 20 steps.
+// Scalar branches, 10 per wave: no time that could be measured.
 __device__ __forceinline__ void end_block(const KP& k)
 {
     if (k.t < 0) asm volatile("s_nop 0");
@@ -1270,8 +1273,8 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
     // FP32 storage (exact mass, no rounding bias in the pure phases at the
     // 1e-5 parity level); FP32 with 16-bit storage, whose own rounding is four
     // orders larger (the sum of 27 16-bit values is exact in FP32 but for the
-    // widest exponent spreads).  Saves about 70 of the 16-bit kernels' 1 070
-    // VALU instructions per wave.
+    // widest exponent spreads).  It saved about 70 VALU
+    // instructions per wave of the 16-bit kernels (858 now).
     using H = typename std::conditional<sizeof(typename S::T) == 4, double, float>::type;
     // raw moments of d up to second order
     H m0s = (H)d[0];
@@ -1400,8 +1403,8 @@ __device__ __forceinline__ void collide_store(const KP& k, const Node& nd, const
     const float K1 = rhof * (3.f - 4.5f * u2);
     const float r45 = 4.5f * rhof;
     typename S::T down[9];  // the populations that leave downwards (slots 0..8)
-    // the order of one sum, written out for the same reason as end_block: which of the
-    // two terms is rounded by itself
+    // the order of one sum, for the same reason as end_block: which of its two terms is
+    // rounded by itself follows what the compiler chose before the sum was written out
     constexpr bool kForceLast = sizeof(typename S::T) == 4 || S::kEqRef || BC == LBM_BC_PERIODIC;
 #pragma unroll
     for (int i = 1; i < Q; i += 2) {

@@ -15,7 +15,7 @@
 // bound by memory traffic, and FP32 arithmetic would add about 1e-5 of the
 // spurious velocity of a resting droplet to the FP32 storage floor).
 // Layout, tiles, windows and walls are those of the D3Q27 kernels (rows without
-// x ghosts, a wavefront inside one row, the jet's ghost plane z = -1): against
+// x ghosts, a wavefront inside one row but on narrow rows, the jet's ghost plane z = -1): against
 // per-thread wrapped indices and neighbours through the caches the step on the
 // 128x128x512 jet went from 0.61 to 0.46 ms.  The collision is bound by
 // its FP64 instructions (980 -> 550 per wave by pairs of opposite directions).
