@@ -426,10 +426,9 @@ __device__ __forceinline__ XOff x_offsets(const KP& k, int x)
 // inflow).  The jet's outlet plane is never pulled into; its row above is clamped
 // to stay inside the buffer.
 template <int BC, int CY, int CZ>
-__device__ __forceinline__ void group_source(const KP& k, int y, int z, int& ys, int& zs, bool& my)
+__device__ __forceinline__ uint32_t group_row(const KP& k, int y, int z, bool& my)
 {
-    ys = y - CY;
-    zs = z - CZ;
+    int ys = y - CY, zs = z - CZ;
     my = false;
     if (BC == LBM_BC_PERIODIC) {
         if (CY) ys = wrapc(ys, k.ny);
@@ -441,15 +440,24 @@ __device__ __forceinline__ void group_source(const KP& k, int y, int z, int& ys,
         }
         if (CZ < 0 && zs >= k.nz) zs = k.nz - 1;
     }
+    return row_of(k, ys, zs);
 }
 
-// Element x (a byte offset) of a row of SL slots of rs elements, counted from slot g
-// of row (y, z).  ROW: the row is uniform over the wavefront; else each lane has its
-// own.
-template <int SL, bool ROW, class T>
-__device__ __forceinline__ T ld_slot(const T* __restrict__ base, const KP& k, int y, int z, int g, uint32_t x)
+// element offset of the group in its row; a mirrored row gives the mirrored group
+template <int BC, int SL, int CY, int CZ>
+__device__ __forceinline__ size_t group_off(const KP& k, int y, int z)
 {
-    const T* row = base + ((size_t)row_of(k, y, z) * SL + g) * (uint32_t)k.rs;
+    bool my;
+    const uint32_t row = group_row<BC, CY, CZ>(k, y, z, my);
+    const int g = 9 * (CZ + 1) + 3 * (CY + 1) - (my ? 6 * CY : 0);
+    return ((size_t)row * SL + g) * (uint32_t)k.rs;
+}
+
+// Value at byte offset x of the slots (or records) that begin at `row`.  ROW: the
+// pointer is uniform over the wavefront; else each lane has its own.
+template <bool ROW, class T>
+__device__ __forceinline__ T ld_slot(const T* __restrict__ row, const KP& k, uint32_t x)
+{
     if constexpr (!ROW)
         return *(const T*)((const char*)row + x);
     else if constexpr (sizeof(T) == 16)
@@ -465,11 +473,7 @@ __device__ __forceinline__ typename S::T pull_raw(const typename S::T* __restric
                                                   const XOff& xo)
 {
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
-    int ys, zs;
-    bool my;
-    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
-    const int g = 9 * (cz + 1) + 3 * (cy + 1) - (my ? 6 * cy : 0);  // a mirrored row gives the mirrored group
-    return ld_slot<kSlots<S>, ROW>(src, k, ys, zs, g, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
+    return ld_slot<ROW>(src + group_off<BC, kSlots<S>, cy, cz>(k, y, z), k, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
 }
 
 // A per-node record at (x, y, z), which may lie one node outside: wrapped, or
@@ -531,11 +535,11 @@ __device__ __forceinline__ T pull_rec(const T* __restrict__ base, const KP& k, i
 {
     static_assert(sizeof(T) == 16, "16-byte records");
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
-    int ys, zs;
     bool my;
-    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
+    const uint32_t row = group_row<BC, cy, cz>(k, y, z, my);
     m = (BC == LBM_BC_JET && ((cx > 0 && xo.wp) || (cx < 0 && xo.wm)) ? 1 : 0) | (my ? 2 : 0);
-    return ld_slot<1, ROW>(base, k, ys, zs, 0, cx > 0 ? xo.rp : (cx < 0 ? xo.rm : xo.ro));
+    return ld_slot<ROW>(base + (size_t)row * (uint32_t)k.rs, k,
+                        cx > 0 ? xo.rp : (cx < 0 ? xo.rm : xo.ro));
 }
 
 // pre-collision deviation d_I pulled into node (x, y, z)
@@ -546,9 +550,9 @@ __device__ __forceinline__ float pull_dev(const typename S::T* __restrict__ src,
     if constexpr (!S::kEqRef) {
         return S::dec(pull_raw<BC, S, I, ROW>(src, k, y, z, xo));
     } else if constexpr (I == 0 && !ROW) {
-        const uint32_t xB = (uint32_t)x * (uint32_t)sizeof(typename S::T);
-        const uint32_t hi = __builtin_bit_cast(uint16_t, ld_slot<kSlots<S>, false>(src, k, y, z, slot_of(0), xB));
-        const uint32_t lo = __builtin_bit_cast(uint16_t, ld_slot<kSlots<S>, false>(src, k, y, z, Q, xB));
+        const typename S::T* b = src + (size_t)row_of(k, y, z) * (kSlots<S> * (uint32_t)k.rs) + x;
+        const uint32_t hi = __builtin_bit_cast(uint16_t, b[slot_of(0) * (uint32_t)k.rs]);
+        const uint32_t lo = __builtin_bit_cast(uint16_t, b[Q * (uint32_t)k.rs]);
         return __uint_as_float((hi << 16) | lo);
     } else if constexpr (I == 0) {
         const auto r = row_rsrc(src + (size_t)row_of(k, y, z) * (kSlots<S> * (uint32_t)k.rs),
@@ -756,12 +760,17 @@ inline dim3 tile_grid(int nx, int ny, int planes)
     return dim3((unsigned)row);
 }
 
-// tile b and plane z of block (bx, by) of such a grid (gx, gy); false: beyond the planes
-__host__ __device__ __forceinline__ bool tile_of_block(uint32_t gx, uint32_t gy, uint32_t bx, uint32_t by, int T,
-                                                       int planes, int& b, int& z)
+// tile b and plane z of block (bx, by) of such a grid (gx, gy) of T tiles a plane; not
+// live: beyond the planes
+struct TileOrder {
+    int b, z;
+    bool live;
+};
+__host__ __device__ __forceinline__ TileOrder tile_of_block(uint32_t gx, uint32_t gy, uint32_t bx, uint32_t by, int T,
+                                                            int planes)
 {
-    b = (int)bx;
-    z = (int)by;
+    int b = (int)bx, z = (int)by;
+    bool live = true;
     if (gy == 1 && gx > 8) {
         const int j = b & 7, i = b >> 3, q = i / T;
         b = i - q * T;  // the band's tiles of planes 8 q .. 8 q + 7, plane by plane
@@ -775,10 +784,11 @@ __host__ __device__ __forceinline__ bool tile_of_block(uint32_t gx, uint32_t gy,
             ++z;
         }
         b += lo >> 3;
-        return z < planes;
+        live = z < planes;
+    } else if ((gx & 7u) == 0) {
+        b = (b & 7) * (int)(gx >> 3) + (b >> 3);
     }
-    if ((gx & 7u) == 0) b = (b & 7) * (int)(gx >> 3) + (b >> 3);
-    return true;
+    return TileOrder{b, z, live};
 }
 
 template <int TX, int TY>
@@ -787,11 +797,10 @@ __device__ __forceinline__ Tile this_tile(const KP& k)
     static_assert(TX % 64 == 0, "a wavefront lies in one row");
     Tile t;
     const int ntx = (k.nx + TX - 1) / TX;
-    int b, z;
-    const bool live = tile_of_block(gridDim.x, gridDim.y, blockIdx.x, blockIdx.y,
-                                    (int)tiles_in_plane<TX, TY>(k.nx, k.ny), k.planes, b, z);
-    t.z = z + k.z0;
-    const int ty = live ? b / ntx : (k.ny + TY) / TY + 1, tx = live ? b - ty * ntx : 0;  // idle: beyond every row
+    const TileOrder o = tile_of_block(gridDim.x, gridDim.y, blockIdx.x, blockIdx.y,
+                                      ntx * ((k.ny + TY - 1) / TY), k.planes);
+    t.z = o.z + k.z0;
+    const int ty = o.live ? o.b / ntx : (k.ny + TY) / TY + 1, tx = o.live ? o.b - ty * ntx : 0;  // idle: beyond every row
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // uniform, and so are y and the row
     t.x0 = tx * TX;
     t.y0 = ty * TY;

@@ -164,10 +164,10 @@ __device__ __forceinline__ float pull19(const float* __restrict__ pop, const KP&
     constexpr int cx = kCX[I], cy = kCY[I], cz = kCZ[I];
     // first of the three slots that the offsets count from
     constexpr int base = slot19(I) - cx - 1, mbase = slot19(mirror_dir(I, 2)) - cx - 1;
-    int ys, zs;
     bool my;
-    group_source<BC, cy, cz>(k, y, z, ys, zs, my);
-    return ld_slot<Q19, ROW>(pop, k, ys, zs, my ? mbase : base, cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
+    const uint32_t row = group_row<BC, cy, cz>(k, y, z, my), rs = (uint32_t)k.rs;
+    return ld_slot<ROW>(pop + (size_t)row * (Q19 * rs) + (uint32_t)(my ? mbase : base) * rs, k,
+                        cx > 0 ? xo.p : (cx < 0 ? xo.m : xo.o));
 }
 
 template <int BC, bool ROW = true, int I = 0>

@@ -26,12 +26,12 @@ void visit(int nx, int ny, int planes)
     long long wrong = 0;
     for (uint32_t by = 0; by < g.y; ++by)
         for (uint32_t bx = 0; bx < g.x; ++bx) {
-            int b, z;
-            if (!tile_of_block(g.x, g.y, bx, by, T, planes, b, z)) continue;
-            if (b < 0 || b >= T || z < 0 || z >= planes)
+            const TileOrder o = tile_of_block(g.x, g.y, bx, by, T, planes);
+            if (!o.live) continue;
+            if (o.b < 0 || o.b >= T || o.z < 0 || o.z >= planes)
                 ++wrong;
             else
-                ++seen[(size_t)z * T + b];
+                ++seen[(size_t)o.z * T + o.b];
         }
     for (int s : seen) wrong += s != 1;
     printf("%lld\n", wrong);
