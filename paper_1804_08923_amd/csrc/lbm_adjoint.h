@@ -347,8 +347,10 @@ __device__ __forceinline__ void adj_drop(const GatherRows& g, const XSide& xs, f
 // wave on 256 registers: per-lane 64-bit addresses, mirrored directions by selects per
 // lane, the node map direction by direction.  Rows by scalars and the node map by
 // opposite pairs leave 2000 (620 us), by moments 1570 on 141 registers (590 us), which
-// three waves per SIMD hold (540 us; four spill).  The loads go out before the
-// window's barrier: 130 us slower with the window first.
+// three waves per SIMD hold (540 us; four spill).  dJ/dA's terms in FP64 (perturb_vjp)
+// make it 1730 on 155 registers, 16 us more.  Arithmetic takes 0.65 of the SIMDs' time
+// now (by counters, at 2.4 GHz).  The loads go out before the window's barrier: 130 us
+// slower with the window first.
 template <int BC, class TL>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_adj_node(
     const float* __restrict__ MOM, const float* __restrict__ lam_in, const float* __restrict__ ML,

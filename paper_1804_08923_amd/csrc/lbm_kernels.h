@@ -1032,8 +1032,8 @@ constexpr int kDensityWaves = (sizeof(typename S::T) == 2 && !S::kEqRef) ? 8 : 2
 // register count and halve its occupancy).
 // MOMS (the adjoint step from a snapshot): also the raw moments of the pulled
 // deviations into MOM.  A compile-time switch: the moment code would raise the step's
-// registers (FP32: to 90) and with them lower its waves.  330 us on the 128x128x512
-// jet, 176 B of traffic per node at 4.5 TB/s (518 us in the plane-major layout).
+// registers (FP32: to 90) and with them lower its waves.  335 us on the 128x128x512
+// jet, 176 B of traffic per node at 4.4 TB/s (518 us in the plane-major layout).
 template <int BC, class S, class TL, bool MOMS = false>
 __global__ __launch_bounds__(TL::DX* TL::DY) __attribute__((amdgpu_waves_per_eu(kDensityWaves<S>, 8))) void k_density(
     const typename S::T* __restrict__ src, float2* __restrict__ PD, float* __restrict__ XR, KP k,

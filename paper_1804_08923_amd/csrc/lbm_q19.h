@@ -15,10 +15,12 @@
 // bound by memory traffic, and FP32 arithmetic would add about 1e-5 of the
 // spurious velocity of a resting droplet to the FP32 storage floor).
 // Layout, tiles, windows and walls are those of the D3Q27 kernels (rows without
-// x ghosts, a wavefront inside one row but on narrow rows, the jet's ghost plane z = -1): against
-// per-thread wrapped indices and neighbours through the caches the step on the
-// 128x128x512 jet went from 0.61 to 0.46 ms.  The collision is bound by
-// its FP64 instructions (980 -> 550 per wave by pairs of opposite directions).
+// x ghosts, a wavefront inside one row but on narrow rows, the jet's ghost plane
+// z = -1): against per-thread wrapped indices and neighbours through the caches the
+// step on the 128x128x512 jet went from 0.61 to 0.46 ms.  The collision, by pairs of
+// opposite directions, has 550 instead of 980 FP64 instructions per wave; all its
+// vector instructions take half of the SIMDs' time on the 256x256x1024 jet, where it
+// moves 181 B per node at 5.4 TB/s.
 //
 // Reduced collision.  With the paper's rates (s0 = s1 = 0, s2b = s3 = s4 = 1)
 // the GMRT collision plus forcing, f - T^-1 K T (f - feq) + T^-1 (I - K/2) T F'
